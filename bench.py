@@ -30,8 +30,8 @@ VALU_PEAK_WAVE_INSTS = 256 * 4 * 2.4e9 / 4.0
 # committed under profiles/ as a JSON block, with the hash of the kernel
 # sources they were taken from; a source change makes them unusable (null).
 COUNTER_PROFILE = "profiles/stage_fused_counters_by_shape_random_modes_256.md"
-KERNEL_SOURCES = ("paper_2303_03026_amd/csrc/fused.hip", "paper_2303_03026_amd/csrc/device_mhd.h",
-                  "paper_2303_03026_amd/csrc/kernels.h")
+KERNEL_SOURCES = tuple("paper_2303_03026_amd/csrc/" + f for f in (
+    "fused_stage.h", "fused.hip", "device_mhd.h", "kernels.h"))
 
 
 def kernel_hash():

@@ -172,7 +172,9 @@ int amrvac_cfl_dt(amrvac_ctx* c, int slot, double* dt_dev, double* ch_dev, doubl
  * L = flux divergence of the van Leer + GLM + HLL interface fluxes plus the
  * psi damping source -kappa*psi.  dt, c_h, kappa are read from DEVICE
  * pointers (as written by amrvac_cfl_dt).  in must have had its ghosts
- * filled; in != out; out may equal base. */
+ * filled; in != out; out may equal base.  The ghost cells of out hold nothing
+ * of use until the next fill: the fused stage of two ghost layers overwrites
+ * those next to its x faces (it writes whole rows). */
 int amrvac_stage(amrvac_ctx* c, int in_slot, int base_slot, int out_slot, double w,
                  const double* dt_dev, const double* ch_dev, const double* kappa_dev);
 

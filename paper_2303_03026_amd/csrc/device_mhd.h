@@ -66,6 +66,59 @@ __device__ __forceinline__ double div_(double a, double b) {
 }
 __device__ __forceinline__ float div_(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
+// Third-order refinement of the seed: with e = 1 - x r, 1/x = r (1 + e + e^2
+// + ...), so two multiply-adds give r (1 + e + e^2), e^3 ~ 2^-73 off: one
+// operation less than two Newton steps and a shorter chain.
+__device__ __forceinline__ double rcp3_(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+__device__ __forceinline__ float rcp3_(float x) { return __builtin_amdgcn_rcpf(x); }
+
+// 1/x and 1/y.  FP64: from one reciprocal of the product (the seed and its
+// refinement are the costly part: 4 of the 12 issue slots of a quotient are
+// the quarter-rate v_rcp_f64 alone), for operands whose product neither
+// overflows nor underflows.
+__device__ __forceinline__ void rcp_pair(double x, double y, double& ix, double& iy) {
+  const double r = rcp3_(x * y);
+  ix = r * y;
+  iy = r * x;
+}
+__device__ __forceinline__ void rcp_pair(float x, float y, float& ix, float& iy) {
+  ix = __builtin_amdgcn_rcpf(x);
+  iy = __builtin_amdgcn_rcpf(y);
+}
+
+// Square root of max(x, 0) (of 1e-300 in FP64, where the seed needs a
+// positive operand); a NaN gives 0 as well.  FP64: with y the seed, g = x y
+// and e = 1 - g y, sqrt(x) = g (1 - e)^(-1/2) = g (1 + e/2 + 3/8 e^2), e^3
+// ~ 2^-72 off.
+__device__ __forceinline__ double sqrt_pos(double x) {
+  x = fmax(x, 1e-300);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double e = fma(-g, y, 1.0);
+  return fma(g, e * fma(e, 0.375, 0.5), g);
+}
+__device__ __forceinline__ float sqrt_pos(float x) { return __builtin_amdgcn_sqrtf(fmaxf(x, 0.0f)); }
+
+// The same and its reciprocal (two operations more).
+__device__ __forceinline__ double sqrt_rsqrt_pos(double x, double& inv) {
+  x = fmax(x, 1e-300);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double e = fma(-g, y, 1.0);
+  const double t = e * fma(e, 0.375, 0.5);
+  inv = fma(y, t, y);
+  return fma(g, t, g);
+}
+__device__ __forceinline__ float sqrt_rsqrt_pos(float x, float& inv) {
+  const float r = __builtin_amdgcn_sqrtf(fmaxf(x, 0.0f));
+  inv = __builtin_amdgcn_rcpf(r);
+  return r;
+}
+
 __device__ __forceinline__ double sqrt_(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
@@ -127,47 +180,128 @@ __device__ __forceinline__ void prim_to_cons(const double w[NV], double u[NV], c
   u[I_PSI] = w[I_PSI];
 }
 
-// van Leer's harmonic-mean slope.  The quotient is formed for every lane and
-// then selected (no branch), so the nine slopes of a cell can interleave; it
-// is discarded where dm * dp <= 0, which includes a zero denominator.
-template <class R>
-__device__ __forceinline__ R vl_slope(R dm, R dp) {
-  const R q = dm * dp;
-  const R v = div_(R(2) * q, dm + dp);
-  return q > R(0) ? v : R(0);
-}
-
 // Limiters of Table t:limiters that work on the 2-ghost-cell stencil.  With
 // d- = w_i - w_(i-1) and d+ = w_(i+1) - w_i, cell i's face values are
 //   right face:  w_i + lim(d+, d-) / 2,    left face:  w_i - lim(d-, d+) / 2,
 // lim(near, far) being the limited difference across the face (odd in its
 // arguments).  van Leer's is symmetric: lim(d+, d-) = lim(d-, d+) = the
-// harmonic slope.  Koren's and Cada-Torrilhon's third-order ones are not;
-// written division-free with s = sign(near), b = |near|, a = s far, they are
+// harmonic slope 2 d- d+ / (d- + d+), zero where d- d+ <= 0.  Koren's and
+// Cada-Torrilhon's third-order ones are not; written division-free with
+// s = sign(near), b = |near|, a = s far, they are
 //   koren:  s max(0, min(2a, (2b + a)/3, 2b))
 //   cada3:  s max(0, min((2b + a)/3, max(-a/2, min(2a, (2b + a)/3, 1.6 b))))
 // (the unlimited third-order value (2b + a)/3 in smooth monotone regions).
+// The functions below give half of them, the quantity a face value takes.
 enum { LIM_VANLEER = 0, LIM_KOREN = 1, LIM_CADA3 = 2, LIM_WENO5 = 3, LIM_WENOZ5 = 4, LIM_MP5 = 5, LIM_WENOZP5 = 6 };
 
-template <int LIM, class R>
-__device__ __forceinline__ R lim_diff(R near, R far) {
-  const R s = near < R(0) ? R(-1) : R(1);
-  const R b = s * near, a = s * far;
-  const R p3 = (R(2) * b + a) * R(1.0 / 3.0);
-  if (LIM == LIM_KOREN) return s * fmax(R(0), fmin(fmin(R(2) * a, p3), R(2) * b));
-  return s * fmax(R(0), fmin(p3, fmax(R(-0.5) * a, fmin(fmin(R(2) * a, p3), R(1.6) * b))));
+// v with its sign flipped where that of s is set, without a multiplication
+__device__ __forceinline__ double flip_sign(double v, double s) {
+  const long long m = __double_as_longlong(s) & (long long)0x8000000000000000ull;
+  return __longlong_as_double(__double_as_longlong(v) ^ m);
+}
+__device__ __forceinline__ float flip_sign(float v, float s) {
+  return __int_as_float(__float_as_int(v) ^ (__float_as_int(s) & (int)0x80000000));
 }
 
-// Limited differences of a cell for its right (inc_r) and left (inc_l)
-// face values: w + inc_r / 2 and w - inc_l / 2.
+// Koren's and Cada and Torrilhon's, one side.  (Koren's two sides share the
+// smaller of |d-| and |d+|, but an evaluation of both at once holds more
+// values: in FP64 with HLLD it spilled 55 against 19 registers and a 96^3
+// step took 0.41 against 0.28 ms.)
+template <class R>
+__device__ __forceinline__ R koren_half(R near, R far) {
+  const R b = fabs(near), a = flip_sign(far, near);
+  const R p3 = (R(2) * b + a) * R(1.0 / 6.0);
+  return flip_sign(fmax(R(0), fmin(fmin(a, p3), b)), near);
+}
+template <class R>
+__device__ __forceinline__ R cada3_half(R near, R far) {
+  const R b = fabs(near), a = flip_sign(far, near);
+  const R p3 = (R(2) * b + a) * R(1.0 / 6.0);
+  return flip_sign(fmax(R(0), fmin(p3, fmax(R(-0.25) * a, fmin(fmin(a, p3), R(0.8) * b)))), near);
+}
+
+// van Leer's half slope d- d+ / (d- + d+) of two variables of a cell.
+// FP64: one reciprocal serves both quotients (9 against 15 issue slots per
+// slope with a quotient and a select each); the product is clamped at zero
+// instead of selecting, and the sums are kept off zero by 1e-150 (the range
+// of the products is that of d- d+ itself, about 1e-150 to 1e150).  FP32:
+// the reciprocal is one instruction and the range too short for products.
+constexpr double kSlopeTiny = 1e-150;
+__device__ __forceinline__ void vl_half2(double dm1, double dp1, double dm2, double dp2, double& h1, double& h2) {
+  const double s1 = (dm1 + dp1) + kSlopeTiny, s2 = (dm2 + dp2) + kSlopeTiny;
+  const double q1 = fmax(dm1 * dp1, 0.0), q2 = fmax(dm2 * dp2, 0.0);
+  double i1, i2;
+  rcp_pair(s1, s2, i1, i2);
+  h1 = q1 * i1;
+  h2 = q2 * i2;
+}
+__device__ __forceinline__ double vl_half(double dm, double dp) {
+  return fmax(dm * dp, 0.0) * rcp3_((dm + dp) + kSlopeTiny);
+}
+__device__ __forceinline__ float vl_half(float dm, float dp) {
+  const float q = dm * dp;
+  const float v = div_(q, dm + dp);
+  return q > 0.0f ? v : 0.0f;
+}
+__device__ __forceinline__ void vl_half2(float dm1, float dp1, float dm2, float dp2, float& h1, float& h2) {
+  h1 = vl_half(dm1, dp1);
+  h2 = vl_half(dm2, dp2);
+}
+
+// Half the limited differences of a variable (a pair of variables) of a
+// cell, for its right (r) and left (l) face values w + r and w - l.
 template <int LIM, class R>
-__device__ __forceinline__ void cell_increments(R dm, R dp, R& inc_r, R& inc_l) {
+__device__ __forceinline__ void half_increments1(R dm, R dp, R& r, R& l) {
   if (LIM == LIM_VANLEER) {
-    inc_r = vl_slope(dm, dp);
-    inc_l = inc_r;
+    r = vl_half(dm, dp);
+    l = r;
+  } else if (LIM == LIM_KOREN) {
+    r = koren_half(dp, dm);
+    l = koren_half(dm, dp);
   } else {
-    inc_r = lim_diff<LIM>(dp, dm);
-    inc_l = lim_diff<LIM>(dm, dp);
+    r = cada3_half(dp, dm);
+    l = cada3_half(dm, dp);
+  }
+}
+template <int LIM, class R>
+__device__ __forceinline__ void half_increments2(R dm1, R dp1, R dm2, R dp2, R& r1, R& l1, R& r2, R& l2) {
+  if (LIM == LIM_VANLEER) {
+    vl_half2(dm1, dp1, dm2, dp2, r1, r2);
+    l1 = r1;
+    l2 = r2;
+  } else {
+    half_increments1<LIM>(dm1, dp1, r1, l1);
+    half_increments1<LIM>(dm2, dp2, r2, l2);
+  }
+}
+
+// The pairs of variables that share a reciprocal: (rho, p), (v_x, v_y),
+// (v_z, psi), (B_x, B_y); B_z is on its own.  They are the same in every
+// direction and map onto themselves when x and y are exchanged, so that a
+// cell's face values do not depend on where they are evaluated.
+constexpr int kPairs = 5;
+__host__ __device__ constexpr int pair_a(int u) { return (0x75310 >> (4 * u)) & 15; }
+__host__ __device__ constexpr int pair_b(int u) { return (0x76824 >> (4 * u)) & 15; }
+
+// For every variable q of a cell: f(q, w, r, l) with the cell's value w and
+// its half increments; get(q, m, w, p) gives the cell and its neighbours.
+// (pair by pair, so that few of the operands are live at a time)
+template <int LIM, class R, class Get, class F>
+__device__ __forceinline__ void for_increments(Get get, F f) {
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    const int a = pair_a(u), b = pair_b(u);
+    R m1, w1, p1, r1, l1;
+    get(a, m1, w1, p1);
+    if (u < kPairs - 1) {
+      R m2, w2, p2, r2, l2;
+      get(b, m2, w2, p2);
+      half_increments2<LIM>(w1 - m1, p1 - w1, w2 - m2, p2 - w2, r1, l1, r2, l2);
+      f(b, w2, r2, l2);
+    } else {
+      half_increments1<LIM>(w1 - m1, p1 - w1, r1, l1);
+    }
+    f(a, w1, r1, l1);
   }
 }
 
@@ -204,69 +338,88 @@ __device__ __forceinline__ double cell_rate(const double u[NV], const PhysConst&
   return rate;
 }
 
+// Axes transverse to D.  The fluxes below write every sum over components in
+// the order normal, first, second transverse axis, so that a y face
+// evaluated as an x face with x and y exchanged gives the same bits.
+template <int D>
+struct Transverse {
+  static constexpr int T1 = D == 0 ? 1 : 0, T2 = D == 2 ? 1 : 2;
+};
+
+// Fast speeds along the normal on both sides of a face with the common
+// normal field (bn2 = B_n^2, t2 = |B_t|^2): c_f^2 = (S + sqrt(S^2 - 4 gamma p
+// B_n^2)) / (2 rho), S = gamma p + B^2, with the radicand written as the sum
+// of squares (gamma p - B^2)^2 + 4 gamma p B_t^2, which does not cancel; the
+// two 1/rho come from one reciprocal.
+template <class R>
+__device__ __forceinline__ void cfast_faces(R rl, R rr, R pl, R pr, R t2l, R t2r, R bn2, R gamma, R& cl, R& cr) {
+  R il, ir;
+  rcp_pair(rl, rr, il, ir);
+  const R gl = gamma * pl, gr = gamma * pr;
+  const R b2l = bn2 + t2l, b2r = bn2 + t2r;
+  const R ml = gl - b2l, mr = gr - b2r;
+  const R dl = ml * ml + (R(4) * gl) * t2l, dr = mr * mr + (R(4) * gr) * t2r;
+  cl = sqrt_pos(((gl + b2l) + sqrt_pos(dl)) * (R(0.5) * il));
+  cr = sqrt_pos(((gr + b2r) + sqrt_pos(dr)) * (R(0.5) * ir));
+}
+
 // Interface flux along D from reconstructed left/right primitive states:
 // GLM interface values of (B_n, psi) from the exact solution of the linear
 // subsystem, then HLL (Davis bounds) on rho, m, e and the tangential B,
-// with B_n replaced on both sides.  half_inv_ch = 0.5 / c_h.  The HLL
-// combination is formed one component at a time so that only the two
-// primitive states and a few per-side scalars stay live.
+// with B_n replaced on both sides.  half_inv_ch = 0.5 / c_h.
+// With a = min(S_L, 0), b = max(S_R, 0), the weight k = -a / (b - a) of the
+// right side and x^ = x_l + k (x_r - x_l), HLL's (b F_l - a F_r + a b (U_r -
+// U_l)) / (b - a) of the advected part F = U v_n is U_l v_n^ + k (v_n,r - b)
+// (U_r - U_l), and of the rest its hat: half the operations of forming both
+// sides' fluxes and U_r - U_l per component, and the differences of the two
+// sides are taken first.  (The pressure term keeps the two products: where
+// nothing but the density varies it then rounds as the quotient does.)
+// F = F_l exactly where S_L >= 0.
 template <int D, class R>
 __device__ __forceinline__ void hll_glm_flux(R wl[NV], R wr[NV], R ch, R half_inv_ch, R gamma, R inv_gm1,
                                              R F[NV]) {
-  constexpr int N = I_BX + D;
+  constexpr int N = I_BX + D, VN = 1 + D;
+  constexpr int T1 = Transverse<D>::T1, T2 = Transverse<D>::T2;
   const R bn = R(0.5) * (wl[N] + wr[N]) - (wr[I_PSI] - wl[I_PSI]) * half_inv_ch;
   const R ps = R(0.5) * (wl[I_PSI] + wr[I_PSI]) - R(0.5) * ch * (wr[N] - wl[N]);
-  wl[N] = bn;
-  wr[N] = bn;
-
-  const R rl = wl[I_RHO], rr = wr[I_RHO];
-  const R b2l = wl[I_BX] * wl[I_BX] + wl[I_BY] * wl[I_BY] + wl[I_BZ] * wl[I_BZ];
-  const R b2r = wr[I_BX] * wr[I_BX] + wr[I_BY] * wr[I_BY] + wr[I_BZ] * wr[I_BZ];
-  const R cl = cfast<D>(wl, rcp_(rl), b2l, gamma);
-  const R cr = cfast<D>(wr, rcp_(rr), b2r, gamma);
-  const R vnl = wl[1 + D], vnr = wr[1 + D];
-  const R sl = fmin(vnl - cl, vnr - cr);
-  const R sr = fmax(vnl + cl, vnr + cr);
-  // F = a fl + b fr + c (ur - ul): (S_R, -S_L, S_L S_R) / (S_R - S_L) in
-  // the subsonic case, (1, 0, 0) if S_L >= 0 and (0, 1, 0) if S_R <= 0
-  const bool use_l = sl >= R(0), use_r = sr <= R(0);
-  const R inv = rcp_(sr - sl);
-  const R ca = use_l ? R(1) : (use_r ? R(0) : sr * inv);
-  const R cb = use_l ? R(0) : (use_r ? R(1) : -sl * inv);
-  const R cc = (use_l || use_r) ? R(0) : sl * sr * inv;
-  auto hll = [&](R ul, R ur, R fl, R fr) { return ca * fl + cb * fr + cc * (ur - ul); };
+  const R bn2 = bn * bn;
+  const R b1l = wl[I_BX + T1], b1r = wr[I_BX + T1], c1l = wl[I_BX + T2], c1r = wr[I_BX + T2];
+  const R t2l = b1l * b1l + c1l * c1l, t2r = b1r * b1r + c1r * c1r;
+  const R b2l = bn2 + t2l, b2r = bn2 + t2r;
+  const R rl = wl[I_RHO], rr = wr[I_RHO], pl = wl[4], pr = wr[4];
+  R cl, cr;
+  cfast_faces(rl, rr, pl, pr, t2l, t2r, bn2, gamma, cl, cr);
+  const R vnl = wl[VN], vnr = wr[VN];
+  const R a = fmin(fmin(vnl - cl, vnr - cr), R(0));
+  const R b = fmax(fmax(vnl + cl, vnr + cr), R(0));
+  const R inv = rcp3_(b - a);
+  const R k = -a * inv;
+  const R dvn = vnr - vnl;
+  const R vh = vnl + k * dvn;      // v_n^
+  const R g = k * (vnr - b);       // weight of U_r - U_l
   // mass
-  const R mnl = rl * vnl, mnr = rr * vnr;
-  F[I_RHO] = hll(rl, rr, mnl, mnr);
-  // energy
+  const R fm = rl * vh + g * (rr - rl);
+  F[I_RHO] = fm;
+  const R rg = rr * g;  // rho_l (v_n^ - g) v_l + rho_r g v_r = fm v_l + rg (v_r - v_l)
+  // normal momentum and energy
+  const R ptl = pl + R(0.5) * b2l, ptr = pr + R(0.5) * b2r;
+  F[VN] = (b * inv) * (ptl - bn2) + k * (ptr - bn2) + (fm * vnl + rg * dvn);
   {
-    const R v2l = wl[1] * wl[1] + wl[2] * wl[2] + wl[3] * wl[3];
-    const R v2r = wr[1] * wr[1] + wr[2] * wr[2] + wr[3] * wr[3];
-    const R el = wl[4] * inv_gm1 + R(0.5) * rl * v2l + R(0.5) * b2l;
-    const R er = wr[4] * inv_gm1 + R(0.5) * rr * v2r + R(0.5) * b2r;
-    const R vbl = wl[1] * wl[I_BX] + wl[2] * wl[I_BY] + wl[3] * wl[I_BZ];
-    const R vbr = wr[1] * wr[I_BX] + wr[2] * wr[I_BY] + wr[3] * wr[I_BZ];
-    const R ptl = wl[4] + R(0.5) * b2l, ptr = wr[4] + R(0.5) * b2r;
-    F[I_EN] = hll(el, er, (el + ptl) * vnl - bn * vbl, (er + ptr) * vnr - bn * vbr);
-    // momentum
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const R ml = rl * wl[1 + c], mr = rr * wr[1 + c];
-      R fl = ml * vnl - wl[I_BX + c] * bn;
-      R fr = mr * vnr - wr[I_BX + c] * bn;
-      if (c == D) {
-        fl += ptl;
-        fr += ptr;
-      }
-      F[I_MX + c] = hll(ml, mr, fl, fr);
-    }
-  }
-  // tangential field
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (c == D) continue;
-    F[I_BX + c] = hll(wl[I_BX + c], wr[I_BX + c], vnl * wl[I_BX + c] - bn * wl[1 + c],
-                      vnr * wr[I_BX + c] - bn * wr[1 + c]);
+    const R u1l = wl[1 + T1], u1r = wr[1 + T1], u2l = wl[1 + T2], u2r = wr[1 + T2];
+    const R v2l = vnl * vnl + u1l * u1l + u2l * u2l;
+    const R v2r = vnr * vnr + u1r * u1r + u2r * u2r;
+    const R el = pl * inv_gm1 + R(0.5) * (rl * v2l + b2l);
+    const R er = pr * inv_gm1 + R(0.5) * (rr * v2r + b2r);
+    const R vbl = vnl * bn + u1l * b1l + u2l * c1l;
+    const R vbr = vnr * bn + u1r * b1r + u2r * c1r;
+    const R hl = ptl * vnl - bn * vbl, hr = ptr * vnr - bn * vbr;
+    F[I_EN] = el * vh + g * (er - el) + (hl + k * (hr - hl));
+    // tangential momentum and field
+    const R dv1 = u1r - u1l, dv2 = u2r - u2l, db1 = b1r - b1l, db2 = c1r - c1l;
+    F[1 + T1] = fm * u1l + rg * dv1 - bn * (b1l + k * db1);
+    F[1 + T2] = fm * u2l + rg * dv2 - bn * (c1l + k * db2);
+    F[I_BX + T1] = b1l * vh + g * db1 - bn * (u1l + k * dv1);
+    F[I_BX + T2] = c1l * vh + g * db2 - bn * (u2l + k * dv2);
   }
   F[N] = ps;
   F[I_PSI] = ch * ch * bn;
@@ -282,86 +435,105 @@ __device__ __forceinline__ void hll_glm_flux(R wl[NV], R wr[NV], R ch, R half_in
 // S_M -/+ |B_n| / sqrt(rho*), and the double-star states between them and the
 // contact.  Only the side of the contact that the interface lies on is
 // assembled: F = F_a + S_a (U*_a - U_a) [+ S*_a (U**_a - U*_a) between the
-// Alfven wave and the contact]; selects (not arithmetic) drop the star terms
-// when every wave moves one way.
+// Alfven wave and the contact].
 template <int D, class R>
 __device__ __forceinline__ void hlld_glm_flux(R wl[NV], R wr[NV], R ch, R half_inv_ch, R gamma, R inv_gm1,
                                               R F[NV]) {
   constexpr int N = I_BX + D;
-  constexpr int T1 = D == 0 ? 1 : 0, T2 = D == 2 ? 1 : 2;  // tangential axes
+  constexpr int T1 = Transverse<D>::T1, T2 = Transverse<D>::T2;
   const R bn = R(0.5) * (wl[N] + wr[N]) - (wr[I_PSI] - wl[I_PSI]) * half_inv_ch;
   const R ps = R(0.5) * (wl[I_PSI] + wr[I_PSI]) - R(0.5) * ch * (wr[N] - wl[N]);
   wl[N] = bn;
   wr[N] = bn;
   const R rl = wl[I_RHO], rr = wr[I_RHO];
   const R ul = wl[1 + D], ur = wr[1 + D];
-  const R b2l = wl[I_BX] * wl[I_BX] + wl[I_BY] * wl[I_BY] + wl[I_BZ] * wl[I_BZ];
-  const R b2r = wr[I_BX] * wr[I_BX] + wr[I_BY] * wr[I_BY] + wr[I_BZ] * wr[I_BZ];
+  const R bn2 = bn * bn;
+  const R t2l = wl[I_BX + T1] * wl[I_BX + T1] + wl[I_BX + T2] * wl[I_BX + T2];
+  const R t2r = wr[I_BX + T1] * wr[I_BX + T1] + wr[I_BX + T2] * wr[I_BX + T2];
+  const R b2l = bn2 + t2l, b2r = bn2 + t2r;
   const R ptl = wl[4] + R(0.5) * b2l, ptr = wr[4] + R(0.5) * b2r;
-  const R cfm = fmax(cfast<D>(wl, rcp_(rl), b2l, gamma), cfast<D>(wr, rcp_(rr), b2r, gamma));
+  R cl, cr;
+  cfast_faces(rl, rr, wl[4], wr[4], t2l, t2r, bn2, gamma, cl, cr);
+  const R cfm = fmax(cl, cr);
   const R sl = fmin(ul, ur) - cfm, sr = fmax(ul, ur) + cfm;
   const R dl = (sl - ul) * rl, dr = (sr - ur) * rr;
-  const R idd = rcp_(dr - dl);
+  const R idd = rcp3_(dr - dl);
   const R sm = (dr * ur - dl * ul - ptr + ptl) * idd;
   const R pts = (dr * ptl - dl * ptr + dl * dr * (ur - ul)) * idd;
-  const R bn2 = bn * bn;
-  // single-star density and tangential parts, both sides
-  R rs[2], vs1[2], vs2[2], bs1[2], bs2[2], isb[2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    const R* w = a ? wr : wl;
-    const R rho = a ? rr : rl, u = a ? ur : ul, sa = (a ? sr : sl) - u, sb = (a ? sr : sl) - sm;
-    isb[a] = rcp_(sb);
-    rs[a] = rho * sa * isb[a];
-    const R den = rho * sa * sb - bn2;
-    const bool deg = fabs(den) <= R(1e-12) * rho * sa * sa;
-    const R iden = rcp_(den);
-    const R f1 = deg ? R(0) : bn * (sm - u) * iden;
-    const R f2 = deg ? R(1) : (rho * sa * sa - bn2) * iden;
-    vs1[a] = w[1 + T1] - f1 * w[I_BX + T1];
-    vs2[a] = w[1 + T2] - f1 * w[I_BX + T2];
-    bs1[a] = f2 * w[I_BX + T1];
-    bs2[a] = f2 * w[I_BX + T2];
+  // single-star density and tangential parts, both sides.  With n = rho
+  // (S - u)^2 - B_n^2 the denominator of the jump conditions is n - rho
+  // (S - u)(S_M - u), so that the cancellation in n enters both terms of
+  // their quotient alike.
+  R isb[2], iden[2], num[2], den[2];
+  rcp_pair(sl - sm, sr - sm, isb[0], isb[1]);
+  num[0] = dl * (sl - ul) - bn2;
+  num[1] = dr * (sr - ur) - bn2;
+  den[0] = num[0] - dl * (sm - ul);
+  den[1] = num[1] - dr * (sm - ur);
+  rcp_pair(den[0], den[1], iden[0], iden[1]);
+  const R rs0 = dl * isb[0], rs1 = dr * isb[1];
+  R f1[2], f2[2];
+  f1[0] = bn * (sm - ul) * iden[0];
+  f1[1] = bn * (sm - ur) * iden[1];
+  f2[0] = num[0] * iden[0];
+  f2[1] = num[1] * iden[1];
+  // the degenerate case is rare: its selects run only in waves that have it
+  const bool deg0 = !(fabs(den[0]) > R(1e-12) * (dl * (sl - ul))), deg1 = !(fabs(den[1]) > R(1e-12) * (dr * (sr - ur)));
+  if (__any(deg0 || deg1)) {
+    asm volatile("");  // keeps the branch wave-uniform
+    iden[0] = rcp3_(den[0]);
+    iden[1] = rcp3_(den[1]);
+    f1[0] = deg0 ? R(0) : bn * (sm - ul) * iden[0];
+    f1[1] = deg1 ? R(0) : bn * (sm - ur) * iden[1];
+    f2[0] = deg0 ? R(1) : num[0] * iden[0];
+    f2[1] = deg1 ? R(1) : num[1] * iden[1];
   }
+  const R v10 = wl[1 + T1] - f1[0] * wl[I_BX + T1], v11 = wr[1 + T1] - f1[1] * wr[I_BX + T1];
+  const R v20 = wl[1 + T2] - f1[0] * wl[I_BX + T2], v21 = wr[1 + T2] - f1[1] * wr[I_BX + T2];
+  const R b10 = f2[0] * wl[I_BX + T1], b11 = f2[1] * wr[I_BX + T1];
+  const R b20 = f2[0] * wl[I_BX + T2], b21 = f2[1] * wr[I_BX + T2];
   // double-star tangential parts
-  const R sql = sqrt_(rs[0]), sqr = sqrt_(rs[1]);
-  const R isum = rcp_(sql + sqr);
+  R isql, isqr;
+  const R sql = sqrt_rsqrt_pos(rs0, isql), sqr = sqrt_rsqrt_pos(rs1, isqr);
+  const R isum = rcp3_(sql + sqr);
   const R sg = bn > R(0) ? R(1) : (bn < R(0) ? R(-1) : R(0));
-  const R vss1 = (sql * vs1[0] + sqr * vs1[1] + (bs1[1] - bs1[0]) * sg) * isum;
-  const R vss2 = (sql * vs2[0] + sqr * vs2[1] + (bs2[1] - bs2[0]) * sg) * isum;
-  const R bss1 = (sql * bs1[1] + sqr * bs1[0] + sql * sqr * (vs1[1] - vs1[0]) * sg) * isum;
-  const R bss2 = (sql * bs2[1] + sqr * bs2[0] + sql * sqr * (vs2[1] - vs2[0]) * sg) * isum;
+  const R sgq = sql * sqr * sg;
+  const R vss1 = (sql * v10 + sqr * v11 + (b11 - b10) * sg) * isum;
+  const R vss2 = (sql * v20 + sqr * v21 + (b21 - b20) * sg) * isum;
+  const R bss1 = (sql * b11 + sqr * b10 + sgq * (v11 - v10)) * isum;
+  const R bss2 = (sql * b21 + sqr * b20 + sgq * (v21 - v20)) * isum;
   // the side a of the contact the interface lies on, and its states
   const bool right = sr < R(0) || (!(sl > R(0)) && sm < R(0));
-  const R* w = right ? wr : wl;
-  const R rho = right ? rr : rl, u = right ? ur : ul, pt = right ? ptr : ptl, b2 = right ? b2r : b2l;
+  const R rho = right ? rr : rl, u = right ? ur : ul, pt = right ? ptr : ptl, p = right ? wr[4] : wl[4];
+  const R u1 = right ? wr[1 + T1] : wl[1 + T1], u2 = right ? wr[1 + T2] : wl[1 + T2];
+  const R c1 = right ? wr[I_BX + T1] : wl[I_BX + T1], c2 = right ? wr[I_BX + T2] : wl[I_BX + T2];
   const R S = right ? sr : sl, sa = S - u;
-  const R rsa = right ? rs[1] : rs[0], isba = right ? isb[1] : isb[0];
-  const R vs1a = right ? vs1[1] : vs1[0], vs2a = right ? vs2[1] : vs2[0];
-  const R bs1a = right ? bs1[1] : bs1[0], bs2a = right ? bs2[1] : bs2[0];
-  const R v2 = w[1] * w[1] + w[2] * w[2] + w[3] * w[3];
-  const R e = w[4] * inv_gm1 + R(0.5) * rho * v2 + R(0.5) * b2;
-  const R vb = w[1] * w[I_BX] + w[2] * w[I_BY] + w[3] * w[I_BZ];
+  const R rsa = right ? rs1 : rs0, isba = right ? isb[1] : isb[0];
+  const R vs1a = right ? v11 : v10, vs2a = right ? v21 : v20;
+  const R bs1a = right ? b11 : b10, bs2a = right ? b21 : b20;
+  const R b2 = bn2 + (c1 * c1 + c2 * c2);
+  const R v2 = u * u + u1 * u1 + u2 * u2;
+  const R e = p * inv_gm1 + R(0.5) * rho * v2 + R(0.5) * b2;
+  const R vb = u * bn + u1 * c1 + u2 * c2;
   const R vbs = sm * bn + vs1a * bs1a + vs2a * bs2a;
   const R es = (sa * e - pt * u + pts * sm + bn * (vb - vbs)) * isba;
   const R vbss = sm * bn + vss1 * bss1 + vss2 * bss2;
-  const R sqa = right ? sqr : sql, sgn_a = right ? R(1) : R(-1);
-  const R ess = es + sgn_a * sqa * (vbs - vbss) * sg;
-  const R sas = sm + sgn_a * fabs(bn) * rcp_(sqa);  // S*_a
-  const bool super = sl > R(0) || sr < R(0);       // every wave moves one way: F = F_a
-  const bool inner = sgn_a * sas > R(0);            // between the Alfven wave and the contact
-  auto hlld = [&](R uq, R usq, R ussq, R fq) {
-    const R fs = fq + S * (usq - uq);
-    const R f = inner ? fs + sas * (ussq - usq) : fs;
-    return super ? fq : f;
-  };
-  F[I_RHO] = hlld(rho, rsa, rsa, rho * u);
-  F[1 + D] = hlld(rho * u, rsa * sm, rsa * sm, rho * u * u + pt - bn2);
-  F[1 + T1] = hlld(rho * w[1 + T1], rsa * vs1a, rsa * vss1, rho * w[1 + T1] * u - w[I_BX + T1] * bn);
-  F[1 + T2] = hlld(rho * w[1 + T2], rsa * vs2a, rsa * vss2, rho * w[1 + T2] * u - w[I_BX + T2] * bn);
-  F[I_EN] = hlld(e, es, ess, (e + pt) * u - bn * vb);
-  F[I_BX + T1] = hlld(w[I_BX + T1], bs1a, bss1, u * w[I_BX + T1] - bn * w[1 + T1]);
-  F[I_BX + T2] = hlld(w[I_BX + T2], bs2a, bss2, u * w[I_BX + T2] - bn * w[1 + T2]);
+  const R sqa = right ? sqr : -sql;  // with the sign of the side
+  const R des = sqa * (vbs - vbss) * sg;  // e** - e*
+  const R sas = sm + fabs(bn) * (right ? isqr : -isql);  // S*_a
+  const bool super = sl > R(0) || sr < R(0);                        // every wave moves one way: F = F_a
+  const bool inner = !super && (right ? sas : -sas) > R(0);          // between the Alfven wave and the contact
+  // F = F_a + S (U* - U_a) + S* (U** - U*): the terms of waves that do not
+  // reach the interface drop by their factor
+  const R s1 = super ? R(0) : S, s2 = inner ? sas : R(0);
+  const R ru = rho * u, m1 = rho * u1, m2 = rho * u2;
+  F[I_RHO] = ru + s1 * (rsa - rho);
+  F[1 + D] = ru * u + pt - bn2 + s1 * (rsa * sm - ru);
+  F[1 + T1] = m1 * u - c1 * bn + s1 * (rsa * vs1a - m1) + s2 * (rsa * (vss1 - vs1a));
+  F[1 + T2] = m2 * u - c2 * bn + s1 * (rsa * vs2a - m2) + s2 * (rsa * (vss2 - vs2a));
+  F[I_EN] = (e + pt) * u - bn * vb + s1 * (es - e) + s2 * des;
+  F[I_BX + T1] = u * c1 - bn * u1 + s1 * (bs1a - c1) + s2 * (bss1 - bs1a);
+  F[I_BX + T2] = u * c2 - bn * u2 + s1 * (bs2a - c2) + s2 * (bss2 - bs2a);
   F[N] = ps;
   F[I_PSI] = ch * ch * bn;
 }
@@ -371,26 +543,30 @@ __device__ __forceinline__ void hlld_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
 // pT* = rho_L (S_L - u_L)(S_M - u_L) + pT_L; both star states take the
 // tangential field and velocity of the HLL average state, and their density,
 // momentum and energy from the jump conditions across S_L or S_R.  Only the
-// side of the contact the interface lies on is assembled; selects drop the
-// star terms when every wave moves one way.
+// side of the contact the interface lies on is assembled.
 template <int D, class R>
 __device__ __forceinline__ void hllc_glm_flux(R wl[NV], R wr[NV], R ch, R half_inv_ch, R gamma, R inv_gm1,
                                               R F[NV]) {
   constexpr int N = I_BX + D;
-  constexpr int T1 = D == 0 ? 1 : 0, T2 = D == 2 ? 1 : 2;
+  constexpr int T1 = Transverse<D>::T1, T2 = Transverse<D>::T2;
   const R bn = R(0.5) * (wl[N] + wr[N]) - (wr[I_PSI] - wl[I_PSI]) * half_inv_ch;
   const R ps = R(0.5) * (wl[I_PSI] + wr[I_PSI]) - R(0.5) * ch * (wr[N] - wl[N]);
   wl[N] = bn;
   wr[N] = bn;
   const R rl = wl[I_RHO], rr = wr[I_RHO];
   const R ul = wl[1 + D], ur = wr[1 + D];
-  const R b2l = wl[I_BX] * wl[I_BX] + wl[I_BY] * wl[I_BY] + wl[I_BZ] * wl[I_BZ];
-  const R b2r = wr[I_BX] * wr[I_BX] + wr[I_BY] * wr[I_BY] + wr[I_BZ] * wr[I_BZ];
+  const R bn2 = bn * bn;
+  const R t2l = wl[I_BX + T1] * wl[I_BX + T1] + wl[I_BX + T2] * wl[I_BX + T2];
+  const R t2r = wr[I_BX + T1] * wr[I_BX + T1] + wr[I_BX + T2] * wr[I_BX + T2];
+  const R b2l = bn2 + t2l, b2r = bn2 + t2r;
   const R ptl = wl[4] + R(0.5) * b2l, ptr = wr[4] + R(0.5) * b2r;
-  const R cl = cfast<D>(wl, rcp_(rl), b2l, gamma), cr = cfast<D>(wr, rcp_(rr), b2r, gamma);
+  R cl, cr;
+  cfast_faces(rl, rr, wl[4], wr[4], t2l, t2r, bn2, gamma, cl, cr);
   const R sl = fmin(ul - cl, ur - cr), sr = fmax(ul + cl, ur + cr);
   // HLL average of density and of the tangential momentum and field
-  const R isr = rcp_(sr - sl);
+  const R dl = (sl - ul) * rl, dr = (sr - ur) * rr;
+  R isr, idd;
+  rcp_pair(sr - sl, dr - dl, isr, idd);
   auto havg = [&](R ql, R qr, R fql, R fqr) { return (sr * qr - sl * ql - (fqr - fql)) * isr; };
   const R rh = havg(rl, rr, rl * ul, rr * ur);
   const R m1h = havg(rl * wl[1 + T1], rr * wr[1 + T1], rl * wl[1 + T1] * ul - wl[I_BX + T1] * bn,
@@ -401,32 +577,36 @@ __device__ __forceinline__ void hllc_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
                      ur * wr[I_BX + T1] - bn * wr[1 + T1]);
   const R b2h = havg(wl[I_BX + T2], wr[I_BX + T2], ul * wl[I_BX + T2] - bn * wl[1 + T2],
                      ur * wr[I_BX + T2] - bn * wr[1 + T2]);
-  const R irh = rcp_(rh);
-  const R vs1 = m1h * irh, vs2 = m2h * irh;
-  const R sm = (rr * ur * (sr - ur) - rl * ul * (sl - ul) + ptl - ptr) * rcp_(rr * (sr - ur) - rl * (sl - ul));
-  const R pts = rl * (sl - ul) * (sm - ul) + ptl;
-  const R vbs = sm * bn + vs1 * b1h + vs2 * b2h;
+  const R sm = (dr * ur - dl * ul + ptl - ptr) * idd;
+  const R pts = dl * (sm - ul) + ptl;
   // the side of the contact the interface lies on
   const bool super = sl >= R(0) || sr <= R(0);
   const bool right = sr <= R(0) || (!(sl >= R(0)) && sm < R(0));
-  const R* w = right ? wr : wl;
-  const R rho = right ? rr : rl, u = right ? ur : ul, pt = right ? ptr : ptl, b2 = right ? b2r : b2l;
-  const R S = right ? sr : sl, sa = S - u, isb = rcp_(S - sm);
-  const R v2 = w[1] * w[1] + w[2] * w[2] + w[3] * w[3];
-  const R e = w[4] * inv_gm1 + R(0.5) * rho * v2 + R(0.5) * b2;
-  const R vb = w[1] * w[I_BX] + w[2] * w[I_BY] + w[3] * w[I_BZ];
+  const R rho = right ? rr : rl, u = right ? ur : ul, pt = right ? ptr : ptl, p = right ? wr[4] : wl[4];
+  const R u1 = right ? wr[1 + T1] : wl[1 + T1], u2 = right ? wr[1 + T2] : wl[1 + T2];
+  const R c1 = right ? wr[I_BX + T1] : wl[I_BX + T1], c2 = right ? wr[I_BX + T2] : wl[I_BX + T2];
+  const R S = right ? sr : sl, sa = S - u;
+  R irh, isb;
+  rcp_pair(rh, S - sm, irh, isb);
+  const R vs1 = m1h * irh, vs2 = m2h * irh;
+  const R vbs = sm * bn + vs1 * b1h + vs2 * b2h;
+  const R b2 = bn2 + (c1 * c1 + c2 * c2);
+  const R v2 = u * u + u1 * u1 + u2 * u2;
+  const R e = p * inv_gm1 + R(0.5) * rho * v2 + R(0.5) * b2;
+  const R vb = u * bn + u1 * c1 + u2 * c2;
+  const R m1 = rho * u1, m2 = rho * u2, ru = rho * u;
   const R rs = rho * sa * isb;
-  const R ms1 = (rho * w[1 + T1] * sa + bn * (w[I_BX + T1] - b1h)) * isb;
-  const R ms2 = (rho * w[1 + T2] * sa + bn * (w[I_BX + T2] - b2h)) * isb;
+  const R ms1 = (m1 * sa + bn * (c1 - b1h)) * isb;
+  const R ms2 = (m2 * sa + bn * (c2 - b2h)) * isb;
   const R es = (e * sa - pt * u + pts * sm + bn * (vb - vbs)) * isb;
-  auto hllc = [&](R uq, R usq, R fq) { return super ? fq : fq + S * (usq - uq); };
-  F[I_RHO] = hllc(rho, rs, rho * u);
-  F[1 + D] = hllc(rho * u, rs * sm, rho * u * u + pt - bn * bn);
-  F[1 + T1] = hllc(rho * w[1 + T1], ms1, rho * w[1 + T1] * u - w[I_BX + T1] * bn);
-  F[1 + T2] = hllc(rho * w[1 + T2], ms2, rho * w[1 + T2] * u - w[I_BX + T2] * bn);
-  F[I_EN] = hllc(e, es, (e + pt) * u - bn * vb);
-  F[I_BX + T1] = hllc(w[I_BX + T1], b1h, u * w[I_BX + T1] - bn * w[1 + T1]);
-  F[I_BX + T2] = hllc(w[I_BX + T2], b2h, u * w[I_BX + T2] - bn * w[1 + T2]);
+  const R s1 = super ? R(0) : S;  // F = F_a + S (U* - U_a), F_a when every wave moves one way
+  F[I_RHO] = ru + s1 * (rs - rho);
+  F[1 + D] = ru * u + pt - bn2 + s1 * (rs * sm - ru);
+  F[1 + T1] = m1 * u - c1 * bn + s1 * (ms1 - m1);
+  F[1 + T2] = m2 * u - c2 * bn + s1 * (ms2 - m2);
+  F[I_EN] = (e + pt) * u - bn * vb + s1 * (es - e);
+  F[I_BX + T1] = u * c1 - bn * u1 + s1 * (b1h - c1);
+  F[I_BX + T2] = u * c2 - bn * u2 + s1 * (b2h - c2);
   F[N] = ps;
   F[I_PSI] = ch * ch * bn;
 }
@@ -481,14 +661,10 @@ __device__ __forceinline__ void positivity_fallback(R wl[NV], R wr[NV], const R 
 template <int LIM, class R>
 __device__ __forceinline__ void reconstruct_face_lim(const R wm[NV], const R wa[NV], const R wb[NV], const R wp[NV],
                                                      R wl[NV], R wr[NV]) {
-#pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    R ra, la, rb, lb;
-    cell_increments<LIM>(wa[q] - wm[q], wb[q] - wa[q], ra, la);
-    cell_increments<LIM>(wb[q] - wa[q], wp[q] - wb[q], rb, lb);
-    wl[q] = wa[q] + R(0.5) * ra;
-    wr[q] = wb[q] - R(0.5) * lb;
-  }
+  for_increments<LIM, R>([&](int q, R& m, R& w, R& p) { m = wm[q]; w = wa[q]; p = wb[q]; },
+                         [&](int q, R w, R r, R) { wl[q] = w + r; });
+  for_increments<LIM, R>([&](int q, R& m, R& w, R& p) { m = wa[q]; w = wb[q]; p = wp[q]; },
+                         [&](int q, R w, R, R l) { wr[q] = w - l; });
   positivity_fallback(wl, wr, wa, wb);
 }
 
@@ -638,6 +814,27 @@ __device__ __forceinline__ void reconstruct_face6(int lim, const R c[6][NV], dou
 // block.  FP64: 9 double arrays.  Mixed: 8 float arrays (rho, m_x, m_y, m_z,
 // B_x, B_y, B_z, psi) then one double array (e).  Values move as double.
 
+// Address of element `off` bytes into the array at base, a wave-uniform
+// address, for the scalar-base form of the global loads and stores (a scalar
+// pair and one 32-bit lane offset).  The empty asm keeps the two apart: the
+// compiler would otherwise add the lane offset first and form a 64-bit lane
+// address for every variable (two VALU additions per access in FP64, where
+// the variables of a block lie 64 KB apart, beyond the immediate offsets).
+template <class T>
+__device__ __forceinline__ T __attribute__((address_space(1))) * lane_ptr(const char* base, unsigned off) {
+  auto* p = (__attribute__((address_space(1))) char*)base;
+  asm("" : "+s"(p));
+  return (T __attribute__((address_space(1)))*)(p + (size_t)off);
+}
+
+// A wave-uniform address the compiler takes as new, so that what is added to
+// it is not formed once before a loop (a block's variables times its slots
+// are more scalar registers than there are).
+__device__ __forceinline__ const void* fresh(const void* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 struct StoreF64 {
   using R = double;  // face arithmetic type
   static constexpr int kBytesPerCell = 72;
@@ -647,6 +844,15 @@ struct StoreF64 {
   }
   __device__ static void st(void* blk, int q, long c, long pc, double v) {
     static_cast<double*>(blk)[q * pc + c] = v;
+  }
+  // the same at cell c of a block whose address is wave-uniform: the
+  // variable's address stays scalar and one 32-bit byte offset per lane
+  // serves all variables
+  __device__ static double ld_at(const void* blk, int q, unsigned c, long pc) {
+    return *lane_ptr<double>(static_cast<const char*>(blk) + q * pc * 8, c * 8u);
+  }
+  __device__ static void st_at(void* blk, int q, unsigned c, long pc, double v) {
+    *lane_ptr<double>(static_cast<const char*>(blk) + q * pc * 8, c * 8u) = v;
   }
   // the value a later load of variable q returns after st(v)
   __device__ static double as_stored(int, double v) { return v; }
@@ -666,6 +872,18 @@ struct StoreMixed {
       reinterpret_cast<double*>(static_cast<char*>(blk) + 32 * pc)[c] = v;
     else
       static_cast<float*>(blk)[fidx(q) * pc + c] = (float)v;
+  }
+  __device__ static double ld_at(const void* blk, int q, unsigned c, long pc) {
+    const char* p = static_cast<const char*>(blk);
+    if (q == I_EN) return *lane_ptr<double>(p + 32 * pc, c * 8u);
+    return (double)*lane_ptr<float>(p + fidx(q) * pc * 4, c * 4u);
+  }
+  __device__ static void st_at(void* blk, int q, unsigned c, long pc, double v) {
+    const char* p = static_cast<const char*>(blk);
+    if (q == I_EN)
+      *lane_ptr<double>(p + 32 * pc, c * 8u) = v;
+    else
+      *lane_ptr<float>(p + fidx(q) * pc * 4, c * 4u) = (float)v;
   }
   __device__ static double as_stored(int q, double v) { return q == I_EN ? v : (double)(float)v; }
 };
