@@ -668,63 +668,75 @@ __device__ __forceinline__ void reconstruct_face_lim(const R wm[NV], const R wa[
   positivity_fallback(wl, wr, wa, wb);
 }
 
-// Fifth-order WENO value at the face between cells i and i+1 seen from cell i
-// (cells i-2 .. i+2; 3 ghost layers): candidate polynomials q_k, smoothness
-// indicators beta_k, optimal weights (0.1, 0.6, 0.3).  Weights by limiter:
-// 'weno5' (Jiang-Shu) d_k / (1e-6 + beta_k)^2; 'wenoz5' (Borges et al.)
-// d_k (1 + tau5 / (beta_k + 1e-40)) with tau5 = |beta_0 - beta_2|;
-// 'wenozp5' (Acker et al.) d_k (1 + (tau5 / (beta_k + 1e-40))^2 + lambda
-// (beta_k + 1e-40) / (tau5 + 1e-40)) with lambda = dx^(2/3).
-__device__ __forceinline__ double weno5_face(double vm2, double vm1, double v0, double vp1, double vp2, int lim,
-                                             double lambda) {
-  const double q0 = (2.0 * vm2 - 7.0 * vm1 + 11.0 * v0) * (1.0 / 6.0);
-  const double q1 = (-vm1 + 5.0 * v0 + 2.0 * vp1) * (1.0 / 6.0);
-  const double q2 = (2.0 * v0 + 5.0 * vp1 - vp2) * (1.0 / 6.0);
-  const double a0 = vm2 - 2.0 * vm1 + v0, b0 = vm2 - 4.0 * vm1 + 3.0 * v0;
-  const double a1 = vm1 - 2.0 * v0 + vp1, b1 = vm1 - vp1;
-  const double a2 = v0 - 2.0 * vp1 + vp2, b2 = 3.0 * v0 - 4.0 * vp1 + vp2;
-  const double be0 = (13.0 / 12.0) * a0 * a0 + 0.25 * b0 * b0;
-  const double be1 = (13.0 / 12.0) * a1 * a1 + 0.25 * b1 * b1;
-  const double be2 = (13.0 / 12.0) * a2 * a2 + 0.25 * b2 * b2;
+// Fifth-order WENO face values of cell i (cells i-2 .. i+2; 3 ghost layers)
+// on its right and its left: candidate polynomials q_k, smoothness indicators
+// beta_k, optimal weights (0.1, 0.6, 0.3).  Weights by limiter: 'weno5'
+// (Jiang-Shu) d_k / (1e-6 + beta_k)^2; 'wenoz5' (Borges et al.) d_k (1 +
+// tau5 / (beta_k + 1e-40)) with tau5 = |beta_0 - beta_2|; 'wenozp5' (Acker et
+// al.) d_k (1 + (tau5 / (beta_k + 1e-40))^2 + lambda (beta_k + 1e-40) /
+// (tau5 + 1e-40)) with lambda = dx^(2/3).
+//
+// The two sides share the beta_k and the unweighted factors of the weights:
+// the left one exchanges the optimal weights of the first and the third
+// stencil.  About 93 issue slots for both against 2 x 82 for each by itself.
+// Everything is written in the differences of neighbouring cells, q_k as v0
+// plus a correction, and every step is symmetric under reversing the cells,
+// so that the left value is bit for bit the right value of the reversed
+// cells.  The beta_k are four times the published ones, and so are the
+// constants added to them (the weights keep their ratios).
+__device__ __forceinline__ void weno5_sides(double vm2, double vm1, double v0, double vp1, double vp2, int lim,
+                                            double lambda, double& right, double& left) {
+  const double d0 = vm1 - vm2, d1 = v0 - vm1, d2 = vp1 - v0, d3 = vp2 - vp1;
+  const double a0 = d1 - d0, a1 = d2 - d1, a2 = d3 - d2;
+  auto beta = [](double a, double b) { return (13.0 / 3.0) * a * a + b * b; };
+  const double be0 = beta(a0, 3.0 * d1 - d0), be1 = beta(a1, d1 + d2), be2 = beta(a2, 3.0 * d2 - d3);
   // the three reciprocals of the weights come from one reciprocal of their
   // product (the refined hardware reciprocal is the costly operation here);
-  // the factors are at least 1e-40 (1e-12 for 'weno5'), so the product does
+  // the factors are at least 4e-40 (1.6e-11 for 'weno5'), so the product does
   // not underflow, and it overflows only for cell values beyond about 1e50
-  auto rcp3 = [](double x0, double x1, double x2, double& r0, double& r1, double& r2) {
-    const double x01 = x0 * x1;
-    const double r = rcp_(x01 * x2);
-    r0 = r * (x1 * x2);
-    r1 = r * (x0 * x2);
-    r2 = r * x01;
+  auto rcp_three = [](double x0, double x1, double x2, double& r0, double& r1, double& r2) {
+    const double x02 = x0 * x2;
+    const double r = rcp3_(x02 * x1);
+    const double t = r * x1;
+    r0 = t * x2;
+    r1 = r * x02;
+    r2 = t * x0;
   };
-  double al0, al1, al2;
+  double g0, g1, g2;
   if (lim == LIM_WENOZ5 || lim == LIM_WENOZP5) {
     const double tau5 = fabs(be0 - be2);
-    const double e0 = be0 + 1e-40, e1 = be1 + 1e-40, e2 = be2 + 1e-40;
+    const double e0 = be0 + 4e-40, e1 = be1 + 4e-40, e2 = be2 + 4e-40;
     double i0, i1, i2;
-    rcp3(e0, e1, e2, i0, i1, i2);
+    rcp_three(e0, e1, e2, i0, i1, i2);
     const double r0 = tau5 * i0, r1 = tau5 * i1, r2 = tau5 * i2;
     if (lim == LIM_WENOZ5) {
-      al0 = 0.1 * (1.0 + r0);
-      al1 = 0.6 * (1.0 + r1);
-      al2 = 0.3 * (1.0 + r2);
+      g0 = 1.0 + r0;
+      g1 = 1.0 + r1;
+      g2 = 1.0 + r2;
     } else {
       // the weights times tau5 + 1e-40 (their ratios are what counts), which
       // takes the quotient lambda / (tau5 + 1e-40) out
-      const double tp = tau5 + 1e-40;
-      al0 = 0.1 * (tp + (tp * r0) * r0 + lambda * e0);
-      al1 = 0.6 * (tp + (tp * r1) * r1 + lambda * e1);
-      al2 = 0.3 * (tp + (tp * r2) * r2 + lambda * e2);
+      const double tp = tau5 + 4e-40;
+      g0 = tp + (tp * r0) * r0 + lambda * e0;
+      g1 = tp + (tp * r1) * r1 + lambda * e1;
+      g2 = tp + (tp * r2) * r2 + lambda * e2;
     }
   } else {
-    const double e0 = 1e-6 + be0, e1 = 1e-6 + be1, e2 = 1e-6 + be2;
-    double i0, i1, i2;
-    rcp3(e0 * e0, e1 * e1, e2 * e2, i0, i1, i2);
-    al0 = 0.1 * i0;
-    al1 = 0.6 * i1;
-    al2 = 0.3 * i2;
+    const double e0 = 4e-6 + be0, e1 = 4e-6 + be1, e2 = 4e-6 + be2;
+    rcp_three(e0 * e0, e1 * e1, e2 * e2, g0, g1, g2);
   }
-  return div_(al0 * q0 + al1 * q1 + al2 * q2, al0 + al1 + al2);
+  // v0 + (al0 c0 + al1 c1 + al2 c2) / (6 (al0 + al1 + al2)), c_k = 6 (q_k - v0)
+  auto value = [&](double ga, double gb, double gc, double ca, double cb, double cc) {
+    const double al0 = 0.1 * ga, al1 = 0.6 * gb, al2 = 0.3 * gc;
+    const double den = al0 + al1 + al2;
+    const double num = (al0 * ca + al1 * cb + al2 * cc) * (1.0 / 6.0);
+    const double r = __builtin_amdgcn_rcp(den);
+    const double e = fma(-den, r, 1.0);
+    const double q = num * r;
+    return v0 + fma(q, fma(e, e, e), q);
+  };
+  right = value(g0, g1, g2, 2.0 * a0 + 3.0 * d1, 3.0 * d2 - a1, 3.0 * d2 - a2);
+  left = value(g2, g1, g0, 2.0 * a2 - 3.0 * d2, -3.0 * d1 - a1, -3.0 * d1 - a0);
 }
 
 __device__ __forceinline__ double mm2(double a, double b) {
@@ -769,18 +781,23 @@ __device__ __forceinline__ void reconstruct_face(int lim, const R wm[NV], const 
     reconstruct_face_lim<LIM_VANLEER>(wm, wa, wb, wp, wl, wr);
 }
 
-// The five-cell face values at face precision R: the stored (R) cell
-// values are promoted and the value is computed in FP64, then rounded to R.
+// The five-cell face values of a cell at face precision R: the stored (R)
+// cell values are promoted and the values computed in FP64, then rounded to R.
 // (In FP32 the WENO-Z+ term (tau5 / (beta + 1e-40))^2 overflows and 1e-40
 // is not representable, so the nonlinear weights stay FP64 on the mixed
 // path too.)
 template <class R>
-__device__ __forceinline__ R weno5_face_r(R vm2, R vm1, R v0, R vp1, R vp2, int lim, double lambda) {
-  return (R)weno5_face((double)vm2, (double)vm1, (double)v0, (double)vp1, (double)vp2, lim, lambda);
-}
-template <class R>
-__device__ __forceinline__ R mp5_face_r(R vm2, R vm1, R v0, R vp1, R vp2) {
-  return (R)mp5_face((double)vm2, (double)vm1, (double)v0, (double)vp1, (double)vp2);
+__device__ __forceinline__ void five_cell_sides(int lim, R vm2, R vm1, R v0, R vp1, R vp2, double lambda, R& right,
+                                                R& left) {
+  double r, l;
+  if (lim == LIM_MP5) {
+    r = mp5_face((double)vm2, (double)vm1, (double)v0, (double)vp1, (double)vp2);
+    l = mp5_face((double)vp2, (double)vp1, (double)v0, (double)vm1, (double)vm2);
+  } else {
+    weno5_sides((double)vm2, (double)vm1, (double)v0, (double)vp1, (double)vp2, lim, lambda, r, l);
+  }
+  right = (R)r;
+  left = (R)l;
 }
 
 // Face states from the six cells c[0..5] around the face between c[2] and
@@ -790,18 +807,12 @@ __device__ __forceinline__ R mp5_face_r(R vm2, R vm1, R v0, R vp1, R vp2) {
 // always.
 template <class R>
 __device__ __forceinline__ void reconstruct_face6(int lim, const R c[6][NV], double lambda, R wl[NV], R wr[NV]) {
-  if (lim == LIM_MP5) {
+  if (lim >= LIM_WENO5) {
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
-      wl[q] = mp5_face_r(c[0][q], c[1][q], c[2][q], c[3][q], c[4][q]);
-      wr[q] = mp5_face_r(c[5][q], c[4][q], c[3][q], c[2][q], c[1][q]);
-    }
-    positivity_fallback(wl, wr, c[2], c[3]);
-  } else if (lim >= LIM_WENO5) {
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      wl[q] = weno5_face_r(c[0][q], c[1][q], c[2][q], c[3][q], c[4][q], lim, lambda);
-      wr[q] = weno5_face_r(c[5][q], c[4][q], c[3][q], c[2][q], c[1][q], lim, lambda);
+      R unused;
+      five_cell_sides(lim, c[0][q], c[1][q], c[2][q], c[3][q], c[4][q], lambda, wl[q], unused);
+      five_cell_sides(lim, c[1][q], c[2][q], c[3][q], c[4][q], c[5][q], lambda, unused, wr[q]);
     }
     positivity_fallback(wl, wr, c[2], c[3]);
   } else {

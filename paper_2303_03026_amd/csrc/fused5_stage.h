@@ -14,8 +14,16 @@
 // (22 x 22 cells, corners unused) live in LDS; halo cells across a face
 // shared with a same-level leaf are read in place from that neighbour's
 // interior, the others from this block's ghost cells (filled by the ghost
-// kernels).  Each thread evaluates one face per in-plane direction;
-// neighbouring face fluxes come by lane shuffles.
+// kernels).  A lane reconstructs one cell per in-plane direction, both of its
+// face values at once (the two share most of a WENO evaluation): the left one
+// is the right state of the cell's left face, the right one goes to the next
+// lane of the 16-lane row, which is a line of the plane (along the second
+// axis the lanes are transposed).  Two things lie outside the rows, the right
+// value of the cell before a line and the left value of the cell after it;
+// each wave forms them for its own lines, one variable of one such cell per
+// lane.  The 17th faces follow in one evaluation per wave and plane, a lane
+// per line.  So every wave does the same work: no wave waits for another's
+// 17th faces.
 //
 // 2D: the block is one x-y plane.  3D: the workgroup first sweeps the 16 x-y
 // planes, leaving each cell's x and y flux differences in a per-block
@@ -38,6 +46,7 @@
 #include <type_traits>
 
 #include "device_mhd.h"
+#include "fused_lanes.h"
 #include "kernels.h"
 
 namespace amrvac {
@@ -47,7 +56,7 @@ constexpr int BN5 = 16;             // cells per block side
 constexpr int NG5 = 3;              // ghost layers
 constexpr int P5 = BN5 + 2 * NG5;   // LDS cells per row / column
 constexpr int S5 = P5 + 1;          // LDS row stride (odd, against bank conflicts on column reads)
-constexpr int NF5 = BN5 + 1;        // faces per line
+constexpr int NF5 = BN5 + 1;        // row stride of the exchanged differences
 
 // padded cell index in a block of the slot layout
 __device__ __forceinline__ long cell5(const GridConst& G, int x, int y, int z = 0) {
@@ -65,14 +74,12 @@ __device__ __forceinline__ long cell5(const GridConst& G, int x, int y, int z = 
 // CFL: also fold the CFL rate of every output cell into the job's running
 // maximum (C.rate_bits, C.nan), leaving out the cells next to faces towards
 // finer leaves when C.skip_fine (the flux correction changes them later).
-// Three workgroups per CU (at most 168 VGPRs; the 3D instances spill a few
-// hundred bytes per lane): a plane's 17th faces leave some waves idle at
-// the barrier after the face evaluations (in the x-z sweep a single wave
-// works through them), and a third resident workgroup fills those slots.
-// With two per CU (256 VGPRs, little spilling) the 3D stage took 12% (FP64)
-// and 24% (FP32-mixed) longer; with four, FP64 lost that gain again.
+// Workgroups per CU (waves per SIMD): three in FP64 (at most 168 VGPRs; the
+// instances take 133 to 168), four in FP32-mixed (128).
+template <class SP>
+constexpr int kWavesPerEU5 = SP::kBytesPerCell == 72 ? 3 : 4;
 template <int NDIM, class SP, bool W1, bool CFL, int LIM, int FLX>
-__global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, JobScalars J, const void* __restrict__ in,
+__global__ void __launch_bounds__(256, kWavesPerEU5<SP>) k_stage_fused5(GridConst G, Tables T, JobScalars J, const void* __restrict__ in,
                                                          const void* base, void* out, double wgt, PhysConst P,
                                                          DevStatus* st, double* __restrict__ part,
                                                          typename SP::R* __restrict__ freg, JobCfl C) {
@@ -82,8 +89,10 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
   // second axis' flux differences to the cells' owners, cell (a, c) at
   // c * NF5 + a
   __shared__ R W[NV][P5 * S5];
-  __shared__ R Ex[NV][BN5];  // the 17th face of each line along the first axis
-  __shared__ R Ey[NV][BN5];  // the 17th face of each line along the second axis
+  // per wave and line (along the first axis 0..3, the second 4..7): the face
+  // values of the cells around the line (the cell before it, the cell after
+  // it) and of its last cell, and the flux of its 17th face
+  __shared__ R Eb[4][8][NV], Ea[4][8][NV], El[4][8][NV], Ef[4][8][NV];
   // mixed: the energy's second-axis differences on their way
   __shared__ double De[std::is_same<typename SP::R, double>::value ? 1 : BN5 * NF5];
   const int b = T.order[blockIdx.x];
@@ -110,8 +119,17 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
     else if (y >= BN5) f = 3;
     else if (NDIM == 3 && z < 0) f = 4;
     else if (NDIM == 3 && z >= BN5) f = 5;
-    if (f >= 0 && lk[f] == LINK_SAME) {
-      blk = block_ptr<SP>(in, ln[f], PC);
+    // (selected, not indexed: a run-time index would place the links in
+    // scratch memory)
+    int kind = -1, nb = b;
+#pragma unroll
+    for (int g = 0; g < 2 * NDIM; ++g)
+      if (f == g) {
+        kind = lk[g];
+        nb = ln[g];
+      }
+    if (kind == LINK_SAME) {
+      blk = block_ptr<SP>(in, nb, PC);
       if (f == 0) xs += BN5;
       else if (f == 1) xs -= BN5;
       else if (f == 2) ys += BN5;
@@ -151,7 +169,7 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
   // store the NV fluxes of one face cell (the address is formed here: the
   // empty asm keeps the compiler from hoisting it out of the plane loops)
   auto put_reg = [&](int f, int cell, const R Fv[NV]) {
-    R* p = freg + ((long)b * 6 + f) * NV * NFC + cell;
+    auto* p = (R __attribute__((address_space(1)))*)(freg + ((long)b * 6 + f) * NV * NFC + cell);
     asm volatile("" : "+v"(p));
 #pragma unroll
     for (int q = 0; q < NV; ++q) p[q * NFC] = Fv[q];
@@ -164,127 +182,186 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
   const double lamy = lim == LIM_WENOZP5 ? 1.0 / cbrt(idy * idy) : 0.0;
   const double lamz = (NDIM == 3 && lim == LIM_WENOZP5) ? 1.0 / cbrt(idz * idz) : 0.0;
 
-  // face f (between cells f-1 and f) of line `line` along the plane's axis
-  // AX, a face of direction D.  The five-cell reconstructions act on one
-  // variable at a time, so each variable's six cells are read from LDS just
-  // before use (a few live registers instead of all 54 values); the
-  // arithmetic is that of the shared six-cell reconstruction.
-  auto face = [&](auto ax, auto dir, int line, int f, double lambda, R Fq[NV]) {
-    constexpr int AX = decltype(ax)::value;
-    constexpr int D = decltype(dir)::value;
-    auto at = [&](int s) {
-      const int a = f - NG5 + s;
-      return AX == 0 ? (line + NG5) * S5 + (a + NG5) : (a + NG5) * S5 + (line + NG5);
-    };
-    R wl[NV], wr[NV];
-    if constexpr (LIM >= LIM_WENO5) {
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        const R v0 = W[q][at(0)], v1 = W[q][at(1)], v2 = W[q][at(2)];
-        const R v3 = W[q][at(3)], v4 = W[q][at(4)], v5 = W[q][at(5)];
-        if constexpr (LIM == LIM_MP5) {
-          wl[q] = mp5_face_r(v0, v1, v2, v3, v4);
-          wr[q] = mp5_face_r(v5, v4, v3, v2, v1);
-        } else {
-          wl[q] = weno5_face_r(v0, v1, v2, v3, v4, lim, lambda);
-          wr[q] = weno5_face_r(v5, v4, v3, v2, v1, lim, lambda);
-        }
-      }
-      R cl[NV], cr[NV];
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        cl[q] = W[q][at(2)];
-        cr[q] = W[q][at(3)];
-      }
-      positivity_fallback(wl, wr, cl, cr);
-    } else {
-      R c1[NV], c2[NV], c3[NV], c4[NV];
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        c1[q] = W[q][at(1)];
-        c2[q] = W[q][at(2)];
-        c3[q] = W[q][at(3)];
-        c4[q] = W[q][at(4)];
-      }
-      reconstruct_face(lim, c1, c2, c3, c4, wl, wr);
-    }
-    face_flux<FLX, D, R>(wl, wr, (R)ch, (R)(0.5 / ch), (R)P.gamma, (R)P.inv_gm1, Fq);
-  };
-  using A0 = std::integral_constant<int, 0>;
-  using A1 = std::integral_constant<int, 1>;
   using DX = std::integral_constant<int, 0>;
   using DY = std::integral_constant<int, 1>;
   using DZ = std::integral_constant<int, 2>;
+  const R chr = (R)ch, hic = (R)(0.5 / ch);
+  // first-order fallback of the face between the plane's cells base and base + s
+  auto fallback = [&](int base, int s, R wl[NV], R wr[NV], int swap) {
+    const bool low = !((wl[I_RHO] > R(0)) && (wl[4] > R(0)) && (wr[I_RHO] > R(0)) && (wr[4] > R(0)));
+    if (__any(low)) {
+      asm volatile("");  // keeps the branch wave-uniform
+      if (low) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+          const int m = swap_xy(q, swap);
+          wl[q] = W[m][base];
+          wr[q] = W[m][base + s];
+        }
+      }
+    }
+  };
+  // f(q, right, left) with both face values of the cell at c, neighbours st
+  // apart, for every variable
+  auto for_sides = [&](int c, int st, double lambda, auto f) {
+    if constexpr (LIM >= LIM_WENO5) {
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        R right, left;
+        five_cell_sides(lim, W[q][c - 2 * st], W[q][c - st], W[q][c], W[q][c + st], W[q][c + 2 * st], lambda, right,
+                        left);
+        // (both values now: the left one is needed only at the flux, and the
+        // compiler would move its evaluation there and keep the operands,
+        // 16 registers per variable instead of two)
+        asm volatile("" : "+v"(left), "+v"(right));
+        f(q, right, left);
+      }
+    } else {
+      auto get = [&](int q, R& m, R& w, R& p) {
+        m = W[q][c - st];
+        w = W[q][c];
+        p = W[q][c + st];
+      };
+      auto put = [&](int q, R w, R r, R l) { f(q, w + r, w - l); };
+      if (lim == LIM_KOREN)
+        for_increments<LIM_KOREN, R>(get, put);
+      else if (lim == LIM_CADA3)
+        for_increments<LIM_CADA3, R>(get, put);
+      else
+        for_increments<LIM_VANLEER, R>(get, put);
+    }
+  };
 
+  // The thread's index as a new value: what is formed from it (the LDS
+  // addresses of a plane's accesses) is then formed in each plane, where it
+  // would otherwise take registers through the plane loops and spill.
+  auto this_lane = [&] {
+    int v = t;
+    if (NDIM == 3) asm volatile("" : "+v"(v));
+    return v;
+  };
   // Flux differences of one plane along its second axis (direction D2) and,
-  // with FIRST, along its first axis (x): 16 x 17 faces per axis on 4 waves.
-  // Along the first axis thread t = (i, j) evaluates the left face of cell
-  // (i, j); along the second it evaluates the lower face of cell (j, i)
-  // (transposed), so that in both directions the next face of a thread's
-  // lies in the next lane of the same wave and reaches it by a lane shuffle.
-  // The 17th faces go to lanes 0..15 of two waves that change with the
-  // plane (first axis and second axis), through LDS: no wave takes more than
-  // three face evaluations.  d1 (first axis) and d2 (second axis) are the
-  // differences F(f+1) - F(f) of cell (i, j).
-  // next - this of two face fluxes: at face precision, the energy's in FP64
+  // with FIRST, along its first axis (x), of this thread's cell (i, j): d2
+  // and d1, F(f+1) - F(f) at face precision, the energy's in FP64.  Along the
+  // first axis lane (i, j) takes the cell (i, j), along the second the cell
+  // (j, i).
+  constexpr bool kMixed = !std::is_same<R, double>::value;
   auto diff = [&](int q, R next, R f) -> double {
     return q == I_EN ? (double)next - (double)f : (double)(next - f);
   };
-  constexpr bool kMixed = !std::is_same<R, double>::value;
   // pl: the plane's index along its normal (register cells pl * 16 + line)
   auto plane_differences = [&](auto first, auto dir2, double lam2, int pl, double d1[NV], double d2[NV]) {
     constexpr bool FIRST = decltype(first)::value;
     constexpr int D2 = decltype(dir2)::value;
     const int rofs = NDIM == 3 ? pl * BN5 : 0;
-    R f1[NV], f2[NV];
-    if constexpr (FIRST) {
-      face(A0{}, DX{}, j, i, lamx, f1);
-      if ((regs & 1u) && i == 0) put_reg(0, rofs + j, f1);
-    }
-    face(A1{}, dir2, j, i, lam2, f2);
-    if ((regs & (1u << (2 * D2))) && i == 0) put_reg(2 * D2, rofs + j, f2);
-    {
-      // the 17th faces: first axis on wave pl % 4, second axis on wave
-      // (pl + 2) % 4, so that the extra pass moves between the SIMDs from
-      // plane to plane (with it always on waves 0 and 1 the 3D stage took
-      // 3% (FP64) and 5% (FP32-mixed) longer)
-      const int wv = t >> 6, ln = t & 63;
-      const int xw = FIRST ? (pl & 3) : -1, yw = (pl + 2) & 3;
-      if ((wv == xw || wv == yw) && ln < BN5) {
-        R fe[NV];
-        if (wv == xw) {
-          if constexpr (FIRST) {
-            face(A0{}, DX{}, ln, BN5, lamx, fe);
-#pragma unroll
-            for (int q = 0; q < NV; ++q) Ex[q][ln] = fe[q];
-            if (regs & 2u) put_reg(1, rofs + ln, fe);
-          }
-        } else {
-          face(A1{}, dir2, ln, BN5, lam2, fe);
-#pragma unroll
-          for (int q = 0; q < NV; ++q) Ey[q][ln] = fe[q];
-          if (regs & (2u << (2 * D2))) put_reg(2 * D2 + 1, rofs + ln, fe);
-        }
+    const int tl = this_lane();
+    const int i = tl & 15, j = tl >> 4, wv = tl >> 6, lane = tl & 63;
+    // cell c (-3 .. 18) of line l along the first (n < 4) or the second axis
+    auto cell_of = [&](int n, int l, int c) {
+      return n < 4 ? (l + NG5) * S5 + (c + NG5) : (c + NG5) * S5 + (l + NG5);
+    };
+    // the face values of the cells around this wave's lines: lane task of
+    // (variable, end, line); the value after a line is the right value of the
+    // reversed cells
+    if constexpr (LIM >= LIM_WENO5) {
+      constexpr int NT = (FIRST ? 16 : 8) * NV;
+#pragma unroll 1
+      for (int task = lane; task < NT; task += 64) {
+        const int q = task / (FIRST ? 16 : 8), n = FIRST ? task & 7 : 4 + (task & 3);
+        const int end = FIRST ? (task >> 3) & 1 : (task >> 2) & 1;
+        const int l = 4 * wv + (n & 3);
+        const int c = cell_of(n, l, end ? BN5 : -1), st = (n < 4 ? 1 : S5) * (end ? -1 : 1);
+        R right, left;
+        five_cell_sides(lim, W[q][c - 2 * st], W[q][c - st], W[q][c], W[q][c + st], W[q][c + 2 * st],
+                        n < 4 ? lamx : lam2, right, left);
+        (end ? Ea : Eb)[wv][n][q] = right;
+      }
+    } else {
+      constexpr int NT = (FIRST ? 16 : 8) * kPairs;
+#pragma unroll 1
+      for (int task = lane; task < NT; task += 64) {
+        const int u = task / (FIRST ? 16 : 8), n = FIRST ? task & 7 : 4 + (task & 3);
+        const int end = FIRST ? (task >> 3) & 1 : (task >> 2) & 1;
+        const int qa = pair_a(u), qb = pair_b(u), l = 4 * wv + (n & 3);
+        const int c = cell_of(n, l, end ? BN5 : -1), st = n < 4 ? 1 : S5;
+        const bool one = u == kPairs - 1;
+        const R a = W[qa][c], am = a - W[qa][c - st], ap = W[qa][c + st] - a;
+        const R b = W[qb][c], bm = one ? R(0.5) : b - W[qb][c - st], bp = one ? R(0.5) : W[qb][c + st] - b;
+        R ra, la, rb, lb;
+        if (lim == LIM_KOREN)
+          half_increments2<LIM_KOREN>(am, ap, bm, bp, ra, la, rb, lb);
+        else if (lim == LIM_CADA3)
+          half_increments2<LIM_CADA3>(am, ap, bm, bp, ra, la, rb, lb);
+        else
+          half_increments2<LIM_VANLEER>(am, ap, bm, bp, ra, la, rb, lb);
+        (end ? Ea : Eb)[wv][n][qa] = end ? a - la : a + ra;
+        if (!one) (end ? Ea : Eb)[wv][n][qb] = end ? b - lb : b + rb;
       }
     }
-    __syncthreads();  // every face evaluated: W is free, Ex / Ey written
-    const int up = (t & 63) + 1;
+    // (read back by the same wave: its LDS accesses stay in order)
+    asm volatile("" ::: "memory");
+    // left faces of this lane's cell along one axis; lane 15 leaves the value
+    // of its line's last cell
+    auto faces = [&](auto second, auto dir, double lam, R F[NV]) {
+      constexpr int A = decltype(second)::value;
+      constexpr int DIR = decltype(dir)::value;
+      constexpr int st = A == 0 ? 1 : S5;
+      const int c = A == 0 ? (j + NG5) * S5 + (i + NG5) : (i + NG5) * S5 + (j + NG5);
+      const int n = 4 * A + (j & 3);
+      R wl[NV], wr[NV];
+      for_sides(c, st, lam, [&](int q, R right, R left) {
+        wl[q] = row_prev(right, Eb[wv][n][q]);
+        wr[q] = left;
+        if (i == BN5 - 1) El[wv][n][q] = right;
+      });
+      fallback(c - st, st, wl, wr, 0);
+      face_flux<FLX, DIR, R>(wl, wr, chr, hic, (R)P.gamma, (R)P.inv_gm1, F);
+      if ((regs & (1u << (2 * DIR))) && i == 0) put_reg(2 * DIR, rofs + j, F);
+    };
+    R f1[NV], f2[NV];
+    if constexpr (FIRST) faces(std::integral_constant<int, 0>{}, DX{}, lamx, f1);
+    faces(std::integral_constant<int, 1>{}, dir2, lam2, f2);
+    asm volatile("" ::: "memory");
+    // the 17th faces of this wave's lines (in the x-y plane a y face is an x
+    // face with x and y exchanged)
+    if (lane < (FIRST ? 8 : 4)) {
+      const int n = FIRST ? lane : 4 + lane, l = 4 * wv + (n & 3);
+      const int sw = FIRST && n >= 4 ? 1 : 0;
+      R wl[NV], wr[NV], F[NV];
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        wl[q] = El[wv][n][swap_xy(q, sw)];
+        wr[q] = Ea[wv][n][swap_xy(q, sw)];
+      }
+      fallback(cell_of(n, l, BN5 - 1), n < 4 ? 1 : S5, wl, wr, sw);
+      face_flux<FLX, FIRST ? 0 : D2, R>(wl, wr, chr, hic, (R)P.gamma, (R)P.inv_gm1, F);
+#pragma unroll
+      for (int q = 0; q < NV; ++q) Ef[wv][n][swap_xy(q, sw)] = F[q];
+      const int face = n < 4 ? 1 : 2 * D2 + 1;
+      if ((regs >> face) & 1u) {
+        auto* p = (R __attribute__((address_space(1)))*)(freg + ((long)b * 6 + face) * NV * NFC + rofs + l);
+        asm volatile("" : "+v"(p));
+#pragma unroll
+        for (int q = 0; q < NV; ++q) p[swap_xy(q, sw) * NFC] = F[q];
+      }
+    }
+    lds_barrier();  // every face evaluated: W is free
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
       if constexpr (FIRST) {
-        const R n1 = __shfl(f1[q], up, 64);
-        d1[q] = diff(q, i < BN5 - 1 ? n1 : Ex[q][j], f1[q]);
+        const R n1 = row_next(f1[q]);
+        d1[q] = diff(q, i < BN5 - 1 ? n1 : Ef[wv][j & 3][q], f1[q]);
       }
-      const R n2 = __shfl(f2[q], up, 64);
+      const R n2 = row_next(f2[q]);
       // second-axis difference of cell (j, i), handed to the thread that owns
       // it (the mixed energy's through a double array)
-      const double dd = diff(q, i < BN5 - 1 ? n2 : Ey[q][j], f2[q]);
+      const double dd = diff(q, i < BN5 - 1 ? n2 : Ef[wv][4 + (j & 3)][q], f2[q]);
       if (kMixed && q == I_EN)
         De[i * NF5 + j] = dd;
       else
         W[q][i * NF5 + j] = (R)dd;
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int q = 0; q < NV; ++q) d2[q] = (kMixed && q == I_EN) ? De[j * NF5 + i] : (double)W[q][j * NF5 + i];
   };
@@ -346,6 +423,7 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
   };
   // the 192 in-plane halo cells of an x-y plane z: 48 per side, 3 layers of 16
   auto fetch_xy_halo = [&](int z, bool count) {
+    const int t = this_lane();
     if (t < 4 * NG5 * BN5) {
       const int side = t / (NG5 * BN5), r = t - side * (NG5 * BN5);
       if (side < 2) {
@@ -363,7 +441,7 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
   if constexpr (NDIM == 2) {
     fetch(i, j, 0, i, j, true);
     fetch_xy_halo(0, true);
-    __syncthreads();
+    lds_barrier();
     double d1[NV], d2[NV], L[NV];
     plane_differences(Yes{}, DY{}, lamy, 0, d1, d2);
 #pragma unroll
@@ -378,9 +456,10 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
     // part[block][var][cell] (interior cells, x fastest)
     double* pb = part + (long)b * NV * (BN5 * BN5 * BN5);
     for (int k = 0; k < BN5; ++k) {
+      const int tl = this_lane(), i = tl & 15, j = tl >> 4;
       fetch(i, j, k, i, j, true);
       fetch_xy_halo(k, false);
-      __syncthreads();
+      lds_barrier();
       double d1[NV], d2[NV];
       plane_differences(Yes{}, DY{}, lamy, k, d1, d2);
       const int ci = (k * BN5 + j) * BN5 + i;
@@ -391,11 +470,13 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
         L = accum(q, L, d2[q], idy);
         pb[q * (BN5 * BN5 * BN5) + ci] = L;
       }
-      __syncthreads();  // the plane's LDS is read before the next plane loads
+      lds_barrier();  // the plane's LDS is read before the next plane loads
     }
+    __syncthreads();  // part is written before other threads read it
     // x-z planes: the z faces (the plane's second axis), then the update;
     // thread (i, j) of plane y owns cell (i, y, j)
     for (int y = 0; y < BN5; ++y) {
+      const int t = this_lane(), i = t & 15, j = t >> 4;
       fetch(i, y, j, i, j, false);
       if (t < 2 * NG5 * BN5) {  // the 96 z-halo cells: 3 layers of 16 below and above
         const int side = t / (NG5 * BN5), r = t - side * (NG5 * BN5);
@@ -403,7 +484,7 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
         const int z = side == 0 ? a - NG5 : BN5 + a;
         fetch(x, y, z, x, z, false);
       }
-      __syncthreads();
+      lds_barrier();
       double d1[NV], d2[NV], L[NV];
       plane_differences(No{}, DZ{}, lamz, y, d1, d2);
       const int ci = (j * BN5 + y) * BN5 + i;
@@ -413,7 +494,7 @@ __global__ void __launch_bounds__(256, 3) k_stage_fused5(GridConst G, Tables T, 
         L[q] = accum(q, L[q], d2[q], idz);
       }
       update(i, y, j, L);
-      __syncthreads();
+      lds_barrier();
     }
   }
   if (CFL) {
