@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libamrvac.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["fused5.hip", "fused5_hllc.hip", "fused5_hlld.hip", "fused.hip", "fused_hllc.hip", "fused_hlld.hip", "plain.hip", "runtime.cpp"]
+SOURCES = ["fused5.hip", "fused5_hllc.hip", "fused5_hlld.hip", "fused.hip", "fused_hllc.hip", "fused_hlld.hip", "block_stage.hip", "plain.hip", "runtime.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-Rpass-analysis=kernel-resource-usage", "-ffp-contract=on", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-munsafe-fp-atomics"]

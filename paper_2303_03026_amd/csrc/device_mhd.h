@@ -655,19 +655,6 @@ __device__ __forceinline__ void positivity_fallback(R wl[NV], R wr[NV], const R 
   }
 }
 
-// Reconstructed left/right states at the face between cells a (=i) and
-// b (=i+1) from four primitive cells m (=i-1), a, b, p (=i+2), with the
-// first-order fallback when rho or p is not positive on either side.
-template <int LIM, class R>
-__device__ __forceinline__ void reconstruct_face_lim(const R wm[NV], const R wa[NV], const R wb[NV], const R wp[NV],
-                                                     R wl[NV], R wr[NV]) {
-  for_increments<LIM, R>([&](int q, R& m, R& w, R& p) { m = wm[q]; w = wa[q]; p = wb[q]; },
-                         [&](int q, R w, R r, R) { wl[q] = w + r; });
-  for_increments<LIM, R>([&](int q, R& m, R& w, R& p) { m = wa[q]; w = wb[q]; p = wp[q]; },
-                         [&](int q, R w, R, R l) { wr[q] = w - l; });
-  positivity_fallback(wl, wr, wa, wb);
-}
-
 // Fifth-order WENO face values of cell i (cells i-2 .. i+2; 3 ghost layers)
 // on its right and its left: candidate polynomials q_k, smoothness indicators
 // beta_k, optimal weights (0.1, 0.6, 0.3).  Weights by limiter: 'weno5'
@@ -768,19 +755,6 @@ __device__ __forceinline__ double mp5_face(double vm2, double vm1, double v0, do
   return u_or + mm2(u_min - u_or, u_max - u_or);
 }
 
-// the same with the limiter chosen at run time (the per-kernel path, and the
-// fused stage with three ghost layers run with a two-ghost-layer limiter)
-template <class R>
-__device__ __forceinline__ void reconstruct_face(int lim, const R wm[NV], const R wa[NV], const R wb[NV],
-                                                 const R wp[NV], R wl[NV], R wr[NV]) {
-  if (lim == LIM_KOREN)
-    reconstruct_face_lim<LIM_KOREN>(wm, wa, wb, wp, wl, wr);
-  else if (lim == LIM_CADA3)
-    reconstruct_face_lim<LIM_CADA3>(wm, wa, wb, wp, wl, wr);
-  else
-    reconstruct_face_lim<LIM_VANLEER>(wm, wa, wb, wp, wl, wr);
-}
-
 // The five-cell face values of a cell at face precision R: the stored (R)
 // cell values are promoted and the values computed in FP64, then rounded to R.
 // (In FP32 the WENO-Z+ term (tau5 / (beta + 1e-40))^2 overflows and 1e-40
@@ -801,23 +775,17 @@ __device__ __forceinline__ void five_cell_sides(int lim, R vm2, R vm1, R v0, R v
 }
 
 // Face states from the six cells c[0..5] around the face between c[2] and
-// c[3] (3 ghost layers): the fifth-order values of 'weno5' / 'wenoz5' /
-// 'wenozp5' (lambda = dx^(2/3) of the block) or 'mp5', else the
-// two-ghost-layer reconstruction from c[1..4]; first-order fallback as
-// always.
+// c[3] (3 ghost layers) by a five-cell reconstruction (lambda = dx^(2/3) of
+// the block), with the first-order fallback.
 template <class R>
 __device__ __forceinline__ void reconstruct_face6(int lim, const R c[6][NV], double lambda, R wl[NV], R wr[NV]) {
-  if (lim >= LIM_WENO5) {
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      R unused;
-      five_cell_sides(lim, c[0][q], c[1][q], c[2][q], c[3][q], c[4][q], lambda, wl[q], unused);
-      five_cell_sides(lim, c[1][q], c[2][q], c[3][q], c[4][q], c[5][q], lambda, unused, wr[q]);
-    }
-    positivity_fallback(wl, wr, c[2], c[3]);
-  } else {
-    reconstruct_face(lim, c[1], c[2], c[3], c[4], wl, wr);
+  for (int q = 0; q < NV; ++q) {
+    R unused;
+    five_cell_sides(lim, c[0][q], c[1][q], c[2][q], c[3][q], c[4][q], lambda, wl[q], unused);
+    five_cell_sides(lim, c[1][q], c[2][q], c[3][q], c[4][q], c[5][q], lambda, unused, wr[q]);
   }
+  positivity_fallback(wl, wr, c[2], c[3]);
 }
 
 // ---------------------------------------------------------------------------

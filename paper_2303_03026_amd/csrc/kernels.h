@@ -82,6 +82,13 @@ hipError_t launch_prolong_faces(hipStream_t s, const GridConst& G, const int* ta
                                 void* slot);
 
 // plain stage (single-job FP64 contexts; scalars are element 0) -------------
+// The limiters of two ghost layers: the whole stage of each block in one
+// workgroup, blocks of 4 .. 16 cells a side with two or three ghost layers;
+// freg (may be null) as for launch_fused_stage.
+hipError_t launch_block_stage(hipStream_t s, const GridConst& G, const Tables& T, const JobScalars& J, const void* in,
+                              const void* base, void* out, double w, const PhysConst& P, DevStatus* st,
+                              double* freg);
+// The five-cell reconstructions: primitives and face fluxes through memory.
 hipError_t launch_prim(hipStream_t s, const GridConst& G, const void* slot, double* prim, const PhysConst& P,
                        DevStatus* st);
 hipError_t launch_flux(hipStream_t s, const GridConst& G, int dir, const double* prim, double* flux,

@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(256) k_prim(GridConst G, const double* __restr
 }
 
 // ---------------------------------------------------------------------------
-// face fluxes along D: one thread per face
+// face fluxes along D of the five-cell reconstructions: one thread per face
 
 template <int D>
 __global__ void __launch_bounds__(256) k_flux(GridConst G, const double* __restrict__ prim, double* __restrict__ flux,
@@ -317,36 +317,18 @@ __global__ void __launch_bounds__(256) k_flux(GridConst G, const double* __restr
   }
   const double* base = prim + (long)b * NV * G.pcells;
   double wl[NV], wr[NV], F[NV];
-  if (G.ng == 3) {  // six-cell stencil f-3 .. f+2
-    double c6[6][NV];
+  // six-cell stencil f-3 .. f+2
+  double c6[6][NV];
 #pragma unroll
-    for (int s = 0; s < 6; ++s) {
-      const int a = f - 3 + s;
-      const long ix = D == 0 ? pidx(G, a, j, k) : (D == 1 ? pidx(G, i, a, k) : pidx(G, i, j, a));
+  for (int s = 0; s < 6; ++s) {
+    const int a = f - 3 + s;
+    const long ix = D == 0 ? pidx(G, a, j, k) : (D == 1 ? pidx(G, i, a, k) : pidx(G, i, j, a));
 #pragma unroll
-      for (int q = 0; q < NV; ++q) c6[s][q] = base[q * G.pcells + ix];
-    }
-    // WENO-Z+'s lambda = dx^(2/3) of this block along D
-    const double lambda = P.limiter == LIM_WENOZP5 ? 1.0 / cbrt(inv_dx[3 * b + D] * inv_dx[3 * b + D]) : 0.0;
-    reconstruct_face6(P.limiter, c6, lambda, wl, wr);
-  } else {
-    double wm[NV], wa[NV], wb[NV], wp[NV];
-    long idx[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int a = f - 2 + s;
-      idx[s] = D == 0 ? pidx(G, a, j, k) : (D == 1 ? pidx(G, i, a, k) : pidx(G, i, j, a));
-    }
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      const double* p = base + q * G.pcells;
-      wm[q] = p[idx[0]];
-      wa[q] = p[idx[1]];
-      wb[q] = p[idx[2]];
-      wp[q] = p[idx[3]];
-    }
-    reconstruct_face(P.limiter, wm, wa, wb, wp, wl, wr);
+    for (int q = 0; q < NV; ++q) c6[s][q] = base[q * G.pcells + ix];
   }
+  // WENO-Z+'s lambda = dx^(2/3) of this block along D
+  const double lambda = P.limiter == LIM_WENOZP5 ? 1.0 / cbrt(inv_dx[3 * b + D] * inv_dx[3 * b + D]) : 0.0;
+  reconstruct_face6(P.limiter, c6, lambda, wl, wr);
   const double ch = *ch_dev;
   face_flux_rt<D, double>(P.flux, wl, wr, ch, 0.5 / ch, P.gamma, P.inv_gm1, F);
   double* out = flux + (long)b * NV * G.nfaces + fi;

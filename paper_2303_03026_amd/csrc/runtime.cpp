@@ -779,11 +779,15 @@ bool can_carry(const amrvac_ctx* c) {
   return c->path == AMRVAC_PATH_FUSED && !(c->G.ng == 3 && c->G.ndim == 3);
 }
 
-// flux registers for the fused stage, when a coarse/fine correction follows
-// it (else null)
-void* stage_freg(const amrvac_ctx* c) {
-  return c->path == AMRVAC_PATH_FUSED && c->n_trefl > 0 ? c->d_freg : nullptr;
-}
+// The per-kernel path's limiters of two ghost layers run as one kernel per
+// stage (launch_block_stage), which corrects coarse/fine fluxes from flux
+// registers as the fused stages do; the five-cell ones pass primitives and
+// face fluxes through memory, whose six-cell stencil would need more LDS than
+// a block's plane.
+bool block_staged(const amrvac_ctx* c) { return c->P.limiter < LIM_WENO5; }
+
+// flux registers for a stage that a coarse/fine correction follows (else null)
+void* stage_freg(const amrvac_ctx* c) { return c->n_trefl > 0 ? c->d_freg : nullptr; }
 
 int clear_if_dirty(amrvac_ctx* c) {
   if (c->acc_dirty) {
@@ -808,12 +812,21 @@ int cfl_of_slot(amrvac_ctx* c, int slot, double* dt, double* ch, double* kap) {
   return AMRVAC_OK;
 }
 
-// The per-kernel (plain) FP64 stage on the given primitive and face-flux
-// scratch: conserved -> primitive over interior and face ghost cells, face
-// fluxes per direction, flux correction at coarse/fine faces, update.
+// The per-kernel (plain) FP64 stage: in one kernel with the flux registers
+// freg (needed where a coarse/fine correction follows), or for the five-cell
+// reconstructions on the given primitive and face-flux scratch: conserved ->
+// primitive over interior and face ghost cells, face fluxes per direction,
+// flux correction at coarse/fine faces, update.
 int plain_stage(amrvac_ctx* c, int in, int base, int out, double w, const JobScalars& J, double* prim,
-                double* const flux[3]) {
+                double* const flux[3], void* freg) {
   const Tables T = c->tables();
+  if (block_staged(c)) {
+    HIP_TRY(c, launch_block_stage(c->stream, c->G, T, J, c->slots[in], c->slots[base], c->slots[out], w, c->P,
+                                  c->d_status, static_cast<double*>(freg)));
+    HIP_TRY(c, launch_reflux_apply(c->stream, c->G, T, J, c->d_trefl, c->refl_first, c->refl_count, c->slots[out], w,
+                                   freg));
+    return AMRVAC_OK;
+  }
   HIP_TRY(c, launch_prim(c->stream, c->G, c->slots[in], prim, c->P, c->d_status));
   for (int d = 0; d < c->G.ndim; ++d)
     HIP_TRY(c, launch_flux(c->stream, c->G, d, prim, flux[d], J.ch, c->P, T.inv_dx));
@@ -854,7 +867,7 @@ int stage_any(amrvac_ctx* c, int in, int base, int out, double w, const JobScala
     if (fold) c->carry_slot = out;
     return AMRVAC_OK;
   }
-  return plain_stage(c, in, base, out, w, J, c->d_prim, c->d_flux);
+  return plain_stage(c, in, base, out, w, J, c->d_prim, c->d_flux, stage_freg(c));
 }
 
 // cfl -> [fill -> stage] x nstages on slots 0, 1, 2 with per-job scalars;
@@ -923,23 +936,23 @@ int enqueue_step(amrvac_ctx* c, int nstages, double* dt, double* ch, double* kap
 
 int slots_for_stages(int nstages) { return nstages >= 5 ? 4 : (nstages >= 3 ? 3 : 2); }
 
-// The plain (per-kernel) FP64 path's primitive and face-flux scratch, the
-// 3D five-cell fused stage's array of in-plane flux differences, and the
-// flux registers of the fused path on grids with coarse/fine flux
+// The five-cell reconstructions' primitive and face-flux scratch on the plain
+// (per-kernel) path, the 3D five-cell fused stage's array of in-plane flux
+// differences, and the flux registers on grids with coarse/fine flux
 // correction (110 KB per 16^3 block in FP64), allocated on
 // first use of their path: a context that only runs the fused path on a
 // uniform grid holds none of them (the plain scratch for 4096 blocks of
 // 16^3 is 6 GB, the difference array 1.2 GB).  Called by the entry points
 // before they enqueue work, so never inside a graph capture.
 int ensure_plain_scratch(amrvac_ctx* c) {
-  if (c->path == AMRVAC_PATH_FUSED && c->n_trefl > 0 && !c->d_freg) {
+  if ((c->path == AMRVAC_PATH_FUSED || block_staged(c)) && c->n_trefl > 0 && !c->d_freg) {
     const size_t nfc = c->G.ndim == 3 ? (size_t)c->G.nx * c->G.nx : (size_t)c->G.nx;
     const size_t rbytes = c->G.precision == 0 ? sizeof(double) : sizeof(float);
     if (int rc = dev_alloc(c, &c->d_freg, (size_t)c->cap * 6 * NV * nfc * rbytes)) return rc;
   }
   if (c->path == AMRVAC_PATH_FUSED && c->G.ng == 3 && c->G.ndim == 3 && !c->d_part)
     if (int rc = dev_alloc(c, (void**)&c->d_part, (size_t)c->cap * NV * c->G.icells * sizeof(double))) return rc;
-  if (c->path != AMRVAC_PATH_PLAIN || c->d_prim) return AMRVAC_OK;
+  if (c->path != AMRVAC_PATH_PLAIN || block_staged(c) || c->d_prim) return AMRVAC_OK;
   const size_t nb = (size_t)c->cap;
   const size_t pcs = nb * NV * c->G.pcells * sizeof(double);
   const size_t fcs = nb * NV * c->G.nfaces * sizeof(double);
@@ -1229,7 +1242,10 @@ int amrvac_stage_noalloc(amrvac_ctx* c, int in, int base, int out, double w, con
   double* flux[3] = {nullptr, nullptr, nullptr};
   for (int d = 0; d < c->G.ndim; ++d) flux[d] = reinterpret_cast<double*>(p + prim_bytes + (size_t)d * flux_bytes);
   touch_slot(c, out);
-  return plain_stage(c, in, base, out, w, JobScalars{dt_dev, ch_dev, kappa_dev}, reinterpret_cast<double*>(p), flux);
+  // (the flux registers of a stage in one kernel take less than the
+  // primitives it does not store)
+  return plain_stage(c, in, base, out, w, JobScalars{dt_dev, ch_dev, kappa_dev}, reinterpret_cast<double*>(p), flux,
+                     c->n_trefl > 0 ? p : nullptr);
 }
 
 int amrvac_combine(amrvac_ctx* c, int a, int b, double coef, int out) {
