@@ -6,24 +6,26 @@
 // It replaces launches that passed primitives and face fluxes through memory
 // (a padded state written and read once per direction, three face arrays
 // written and read: about 15 times the state, where this reads it once, with
-// its ghost cells, and writes it once).  Van Leer + HLL, one SSPRK(2,2) step
-// with CFL and ghost fill, before -> now: 512 blocks of 8^3 715 -> 311 us, of
-// 16^3 4949 -> 1856 us; 1024 2D blocks of 8^2 (cada3 + HLLC) 73 -> 40 us per
-// step; 2309 blocks of 8^3 on three levels 2031 -> 926 us.  Bound by issue:
-// three faces per cell at two waves per SIMD (the 3D instances use all 256
+// its neighbours' rims, and writes it once).  Van Leer + HLL, one SSPRK(2,2)
+// step with CFL and ghost fill, before -> now: 512 blocks of 8^3 713 -> 187 us
+// (311 while the ghost cells of same-level faces were still filled), of 16^3
+// 4959 -> 1199 us; 1024 2D blocks of 8^2 (cada3 + HLLC) 73 -> 37 us per step;
+// 2309 blocks of 8^3 on three levels 2033 -> 582 us.  Bound by issue: three
+// faces per cell at two waves per SIMD (the 3D instances use all 256
 // registers), with the halo cells and far faces of short lines on top.
 //
 // Thread t of a workgroup owns the column (i, j) = (t % nx, t / nx) and
 // marches through its planes; the z stencil is a register queue (as in the
 // fused stage) and the x and y stencils read one LDS plane with its two-deep
-// halo, filled from the block's own ghost cells.  A thread evaluates the left
+// halo, filled from same-level neighbours in place and from the block's ghost
+// cells on its other faces.  A thread evaluates the left
 // x face and the lower y face of its cell; rows and waves do not coincide
 // here, so the neighbours' faces come through LDS.  The far faces of the lines
 // are evaluated once per plane, x and y in one pass (a y face is an x face
 // with x and y exchanged).  Short blocks leave lanes idle (4^2 columns are a
 // quarter of a wave); sharing a wave among blocks cost the scalar block
 // address and spilled 18 to 120 registers, and gave nothing on 4096 blocks of
-// 4^3 (791 us either way).
+// 4^3 (791 us either way, with filled ghost cells).
 #include "fused_lanes.h"
 #include "kernels.h"
 
@@ -61,6 +63,17 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
   double* const Fy = Fx + NV * S.cols;
   double* const Xf = Fy + NV * S.cols;
   const double* const U = in + (long)b * NV * PC;
+  // from U to the values outside each face: the ghost cells, or the cells
+  // themselves of a same-level neighbour
+  long* const out_of = reinterpret_cast<long*>(Xf + 2 * NV * nx);
+  auto outside = [&](int f) -> long {
+    const int* L = T.link + ((long)b * 6 + f) * LINK_INTS;
+    if (L[0] != LINK_SAME) return 0;
+    const int step = f < 2 ? 1 : (f < 4 ? pn : pn * pn);
+    return (long)(L[1] - b) * NV * PC + (f & 1 ? -nx : nx) * step;
+  };
+  if (tc < 4) out_of[tc] = outside(tc);
+  const long below = NDIM == 3 ? outside(4) : 0, above = NDIM == 3 ? outside(5) : 0;
   auto cell = [&](int x, int y, int z) { return ((NDIM == 3 ? z + ng : 0) * pn + y + ng) * pn + x + ng; };
   auto at = [&](int x, int y) { return (y + 2) * row + (x + 2) * NV; };
   int bad = 0;
@@ -77,6 +90,9 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
   auto load = [&](const double* s, int c, double u[NV]) {
 #pragma unroll
     for (int q = 0; q < NV; ++q) u[q] = s[q * PC + c];
+  };
+  auto load_z = [&](int i, int j, int z, double u[NV]) {
+    load(U + (z < 0 ? below : z >= nx ? above : 0), cell(i, j, z), u);
   };
   // flux registers of the faces towards finer or coarser leaves
   const int nfc = NDIM == 3 ? nx * nx : nx;
@@ -106,7 +122,7 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
       const int o = side & 1 ? nx + a : -1 - a;
       const int x = side < 2 ? o : n, y = side < 2 ? n : o;
       double u[NV], w[NV];
-      load(U, cell(x, y, z), u);
+      load(U + out_of[side], cell(x, y, z), u);
       convert(u, w, true);
       if (a < 2) {
 #pragma unroll
@@ -153,6 +169,7 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
 
   // z queue: W(k+1), the left state of face k+1/2 and the flux differences,
   // which enter plane k holding -F_z(k-1/2)/dz
+  lds_barrier();  // out_of is there
   double wb[NV], wla[NV], acc[NV];
 #pragma unroll
   for (int q = 0; q < NV; ++q) acc[q] = 0.0;
@@ -165,11 +182,11 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
     for (int q = 0; q < NV; ++q) Wp[at(i, j) + q] = wa[q];
     if (NDIM == 3) {
       double wm2[NV], wm1[NV], wl[NV], wr[NV];
-      load(U, cell(i, j, k0 - 2), u);
+      load_z(i, j, k0 - 2, u);
       convert(u, wm2, k0 == 0);
-      load(U, cell(i, j, k0 - 1), u);
+      load_z(i, j, k0 - 1, u);
       convert(u, wm1, k0 == 0);
-      load(U, cell(i, j, k0 + 1), u);
+      load_z(i, j, k0 + 1, u);
       convert(u, wb, owns(k0 + 1));
       for_increments<LIM, double>([&](int q, double& m, double& w, double& p) { m = wm2[q]; w = wm1[q]; p = wa[q]; },
                                   [&](int q, double w, double r, double) { wl[q] = w + r; });
@@ -186,11 +203,11 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
     }
     if (NDIM == 3 && ng > 2) {
       if (k0 == 0) {
-        load(U, cell(i, j, -3), u);
+        load_z(i, j, -3, u);
         convert(u, wa, true);
       }
       if (k1 == nx) {
-        load(U, cell(i, j, nx + 2), u);
+        load_z(i, j, nx + 2, u);
         convert(u, wa, true);
       }
     }
@@ -206,7 +223,7 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
     const int i = tc % nx, j = tc / nx;
     const int kofs = NDIM == 3 ? k * nx : 0;
     double uc[NV];
-    if (kPrefetch && live) load(U, cell(i, j, k + 2), uc);
+    if (kPrefetch && live) load_z(i, j, k + 2, uc);
     lds_barrier();  // the plane is complete
     if (live) {
       for (int l = tc; l < 2 * nx; l += S.cols) {  // far faces: x lines, then y lines
@@ -242,7 +259,7 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
         double wa[NV], wc[NV], wl[NV], wr[NV];
 #pragma unroll
         for (int q = 0; q < NV; ++q) wa[q] = Wp[at(i, j) + q];
-        if (!kPrefetch) load(U, cell(i, j, k + 2), uc);
+        if (!kPrefetch) load_z(i, j, k + 2, uc);
         convert(uc, wc, owns(k + 2));
         for_increments<LIM, double>([&](int q, double& m, double& w, double& p) { m = wa[q]; w = wb[q]; p = wc[q]; },
                                     [&](int q, double w, double r, double l) {
@@ -290,7 +307,7 @@ hipError_t launch_flux_of(hipStream_t s, const GridConst& G, const Tables& T, co
                           DevStatus* st, double* freg) {
   const unsigned grid = (unsigned)(T.nactive * S.nseg);
   const unsigned threads = (unsigned)((S.cols + 63) / 64 * 64);
-  const size_t bytes = (size_t)NV * (S.row * (S.nx + 4) + 2 * S.cols + 2 * S.nx) * sizeof(double);
+  const size_t bytes = (size_t)NV * (S.row * (S.nx + 4) + 2 * S.cols + 2 * S.nx) * sizeof(double) + 4 * sizeof(long);
 #define AMRVAC_BLOCK_LAUNCH(FX) \
   k_stage_block<NDIM, LIM, FX><<<grid, threads, bytes, s>>>(G, T, J, S, in, base, out, w, P, st, freg)
   if (P.flux == FLUX_HLLD)
@@ -317,7 +334,8 @@ hipError_t launch_block_stage(hipStream_t s, const GridConst& G, const Tables& T
   // Small grids: more, shorter marches, until there is a wave per SIMD (each
   // march converts four planes before its first face, so no further: 512
   // blocks of 8^3 took 311 us per step with 2 marches, 327 with 4; 8 blocks
-  // of 16^3 took 103 us with 4, 62 with 16, and 120 before).
+  // of 16^3 took 103 us with 4, 62 with 16, and 120 before; ghost cells of
+  // same-level faces filled).
   const long waves = (long)T.nactive * ((S.cols + 63) / 64);
   S.nseg = 1;
   while (G.ndim == 3 && S.nseg < G.nx && waves * S.nseg < 1024) ++S.nseg;

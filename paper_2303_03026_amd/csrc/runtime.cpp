@@ -755,14 +755,17 @@ int check_slot(amrvac_ctx* c, int s) {
   return AMRVAC_OK;
 }
 
-int fill_slot(amrvac_ctx* c, int slot) {
+// whole: also the ghost cells that copy a same-level neighbour, which the
+// stages that read those in place do without
+int fill_slot(amrvac_ctx* c, int slot, bool whole) {
   const Tables T = c->tables();
-  const bool fused = c->path == AMRVAC_PATH_FUSED;
-  HIP_TRY(c, launch_fill_faces(c->stream, c->G, fused ? c->d_tfused : c->d_tfill, fused ? c->n_tfused : c->n_tfill,
+  HIP_TRY(c, launch_fill_faces(c->stream, c->G, whole ? c->d_tfill : c->d_tfused, whole ? c->n_tfill : c->n_tfused,
                                T, c->slots[slot], c->P, c->fixed));
   HIP_TRY(c, launch_prolong_faces(c->stream, c->G, c->d_tprol, c->n_tprol, T, c->slots[slot]));
   return AMRVAC_OK;
 }
+
+int fill_slot(amrvac_ctx* c, int slot) { return fill_slot(c, slot, c->path != AMRVAC_PATH_FUSED); }
 
 JobCfl cfl_state(amrvac_ctx* c, double* dt, double* ch, double* kappa) {
   return JobCfl{c->d_rate, c->d_nan, c->d_geom, dt, ch, kappa, c->njob_cap};
@@ -785,6 +788,11 @@ bool can_carry(const amrvac_ctx* c) {
 // face fluxes through memory, whose six-cell stencil would need more LDS than
 // a block's plane.
 bool block_staged(const amrvac_ctx* c) { return c->P.limiter < LIM_WENO5; }
+
+// the ghost cells that a step's own stage of this slot reads
+int fill_for_stage(amrvac_ctx* c, int slot) {
+  return fill_slot(c, slot, c->path == AMRVAC_PATH_PLAIN && !block_staged(c));
+}
 
 // flux registers for a stage that a coarse/fine correction follows (else null)
 void* stage_freg(const amrvac_ctx* c) { return c->n_trefl > 0 ? c->d_freg : nullptr; }
@@ -878,24 +886,24 @@ int enqueue_step(amrvac_ctx* c, int nstages, double* dt, double* ch, double* kap
   const JobScalars J{dt, ch, kap};
   int rc;
   if (nstages == 2) {
-    if ((rc = fill_slot(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, J))) return rc;
-    if ((rc = fill_slot(c, 1)) || (rc = stage_any(c, 1, 0, 0, 0.5, J, true))) return rc;
+    if ((rc = fill_for_stage(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, J))) return rc;
+    if ((rc = fill_for_stage(c, 1)) || (rc = stage_any(c, 1, 0, 0, 0.5, J, true))) return rc;
     return AMRVAC_OK;
   }
   if (nstages == 3) {
-    if ((rc = fill_slot(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, J))) return rc;
-    if ((rc = fill_slot(c, 1)) || (rc = stage_any(c, 1, 0, 2, 0.25, J))) return rc;
-    if ((rc = fill_slot(c, 2)) || (rc = stage_any(c, 2, 0, 0, 2.0 / 3.0, J, true))) return rc;
+    if ((rc = fill_for_stage(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, J))) return rc;
+    if ((rc = fill_for_stage(c, 1)) || (rc = stage_any(c, 1, 0, 2, 0.25, J))) return rc;
+    if ((rc = fill_for_stage(c, 2)) || (rc = stage_any(c, 2, 0, 0, 2.0 / 3.0, J, true))) return rc;
     return AMRVAC_OK;
   }
   if (nstages == 4) {
     // SSPRK(4,3): four stages of dt/2; u3 = u0 + (1/3)((u2 + h L(u2)) - u0)
     JobScalars H = J;
     H.dt_scale = 0.5;
-    if ((rc = fill_slot(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, H))) return rc;
-    if ((rc = fill_slot(c, 1)) || (rc = stage_any(c, 1, 1, 2, 1.0, H))) return rc;
-    if ((rc = fill_slot(c, 2)) || (rc = stage_any(c, 2, 0, 1, 1.0 / 3.0, H))) return rc;
-    if ((rc = fill_slot(c, 1)) || (rc = stage_any(c, 1, 1, 0, 1.0, H, true))) return rc;
+    if ((rc = fill_for_stage(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, H))) return rc;
+    if ((rc = fill_for_stage(c, 1)) || (rc = stage_any(c, 1, 1, 2, 1.0, H))) return rc;
+    if ((rc = fill_for_stage(c, 2)) || (rc = stage_any(c, 2, 0, 1, 1.0 / 3.0, H))) return rc;
+    if ((rc = fill_for_stage(c, 1)) || (rc = stage_any(c, 1, 1, 0, 1.0, H, true))) return rc;
     return AMRVAC_OK;
   }
   // SSPRK(5,4) of Spiteri and Ruuth, Shu-Osher coefficients (alpha_kj for
@@ -920,17 +928,17 @@ int enqueue_step(amrvac_ctx* c, int nstages, double* dt, double* ch, double* kap
   constexpr double c2 = a52 / (1.0 - g4);
   JobScalars S = J;
   S.dt_scale = b10;
-  if ((rc = fill_slot(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, S))) return rc;
+  if ((rc = fill_for_stage(c, 0)) || (rc = stage_any(c, 0, 0, 1, 1.0, S))) return rc;
   S.dt_scale = b21 / a21;
-  if ((rc = fill_slot(c, 1)) || (rc = stage_any(c, 1, 0, 2, a21, S))) return rc;
+  if ((rc = fill_for_stage(c, 1)) || (rc = stage_any(c, 1, 0, 2, a21, S))) return rc;
   S.dt_scale = b32 / a32;
-  if ((rc = fill_slot(c, 2)) || (rc = stage_any(c, 2, 0, 1, a32, S))) return rc;
+  if ((rc = fill_for_stage(c, 2)) || (rc = stage_any(c, 2, 0, 1, a32, S))) return rc;
   S.dt_scale = b43 / a43;
-  if ((rc = fill_slot(c, 1)) || (rc = stage_any(c, 1, 0, 3, a43, S))) return rc;
+  if ((rc = fill_for_stage(c, 1)) || (rc = stage_any(c, 1, 0, 3, a43, S))) return rc;
   touch_slot(c, 1);
   HIP_TRY(c, launch_combine(c->stream, c->G, c->tables(), c->slots[0], c->slots[2], c2, c->slots[1]));
   S.dt_scale = b54 / g4;
-  if ((rc = fill_slot(c, 3)) || (rc = stage_any(c, 3, 1, 0, g4, S, true))) return rc;
+  if ((rc = fill_for_stage(c, 3)) || (rc = stage_any(c, 3, 1, 0, g4, S, true))) return rc;
   return AMRVAC_OK;
 }
 
