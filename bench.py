@@ -31,7 +31,7 @@ VALU_PEAK_WAVE_INSTS = 256 * 4 * 2.4e9 / 4.0
 # sources they were taken from; a source change makes them unusable (null).
 COUNTER_PROFILE = "profiles/stage_fused_counters_by_shape_random_modes_256.md"
 KERNEL_SOURCES = tuple("paper_2303_03026_amd/csrc/" + f for f in (
-    "fused_stage.h", "fused.hip", "device_mhd.h", "kernels.h"))
+    "fused_stage.h", "fused.hip", "fused_lanes.h", "device_mhd.h", "kernels.h"))
 
 
 def kernel_hash():
@@ -47,7 +47,8 @@ def kernel_hash():
 # random modes 256^3): VALU wave-instructions per launch.
 COUNTER_PROFILE5 = "profiles/stage_fused5_wave_states_random_modes_256.md"
 KERNEL_SOURCES5 = tuple("paper_2303_03026_amd/csrc/" + f for f in (
-    "fused5_stage.h", "fused5.hip", "fused5_hllc.hip", "fused5_hlld.hip", "device_mhd.h", "kernels.h"))
+    "fused5_stage.h", "fused5.hip", "fused5_hllc.hip", "fused5_hlld.hip", "fused_lanes.h", "device_mhd.h",
+    "kernels.h"))
 
 
 def kernel_hash5():
@@ -211,11 +212,12 @@ def make_workload(name, n=256, levels=6):
 def roofline(avg_ms, bytes_per_launch, counters, kernel):
     """Roofline of the stage kernel over its live average launch time.  With
     the committed counter profile for these kernel sources and this launch
-    shape, the bound is the VALU issue rate ("alu": VALU wave-instructions
-    per launch from the profile over the launch time, against the 614.4 G/s
-    issue peak), which is what limits the stage; the HBM view (algorithmic
-    bytes per launch against 8 TB/s, and the profile's counter traffic) is
-    kept beside it.  Without a matching profile only the HBM view exists."""
+    shape there are two views, the VALU issue rate ("alu": VALU
+    wave-instructions per launch from the profile over the launch time, against
+    the 614.4 G/s issue peak) and the HBM one (algorithmic bytes per launch
+    against 8 TB/s, and the profile's counter traffic).  The bound is the one
+    whose counters come closer to their peak; the other is kept beside it.
+    Without a matching profile only the HBM view exists."""
     achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9
     traffic, valu = (None, None) if counters is None else counters
     hbm = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -224,9 +226,11 @@ def roofline(avg_ms, bytes_per_launch, counters, kernel):
     if valu is None:
         return dict(hbm, kernel=kernel, avg_launch_ms=avg_ms, valu=None)
     rate = valu / (avg_ms * 1e-3)
-    return {"bound": "alu", "kernel": kernel, "achieved": rate, "peak": VALU_PEAK_WAVE_INSTS,
-            "unit": "VALU wave-instructions/s", "frac": rate / VALU_PEAK_WAVE_INSTS, "traffic": traffic,
-            "avg_launch_ms": avg_ms, "valu_wave_insts_per_launch": valu, "hbm": hbm}
+    alu = {"bound": "alu", "achieved": rate, "peak": VALU_PEAK_WAVE_INSTS, "unit": "VALU wave-instructions/s",
+           "frac": rate / VALU_PEAK_WAVE_INSTS, "valu_wave_insts_per_launch": valu}
+    if traffic is not None and hbm["traffic_frac"] > alu["frac"]:
+        return dict(hbm, kernel=kernel, avg_launch_ms=avg_ms, valu=alu)
+    return dict(alu, kernel=kernel, traffic=traffic, avg_launch_ms=avg_ms, hbm=hbm)
 
 
 def time_grid(w, path, mixed, steps, warmup, tune_mode="auto", graph_pass=False, keep=False, label=None):
