@@ -438,12 +438,12 @@ __global__ void __launch_bounds__(256) k_update(GridConst G, Tables T, const dou
 // registers the stage filled as it evaluated those faces: one thread per
 // (task, coarse face cell) reads the coarse face flux and the fluxes of the
 // 2^(d-1) fine faces behind it (those fine blocks' registers on the opposite
-// face).  A cell next to finer leaves across faces of several directions
-// belongs to the thread of the lowest one, which makes its corrections one
-// after the other.  Bound by its chain of loads (task, link, registers, cell)
+// face).  A cell next to finer leaves across faces of several directions is
+// corrected by the thread of the lowest one, one direction after the other.  Bound by its chain of loads (task, link, registers, cell)
 // and, across x, by partial lines; one launch for all directions overlaps
-// what three in turn did not (step of 2309 blocks of 8^3 on three levels 582
-// -> 559 us, of the 6-level 2D shock cloud in FP32-mixed 393 -> 387 us).
+// what three in turn did not: per stage of 2309 blocks of 8^3 on three levels
+// 32 -> 15 us, of the 6-level 2D shock cloud in FP32-mixed 19 -> 11, of the
+// 3D one (4376 blocks of 16^3) 52 -> 48 (65 with the tasks in block order).
 template <class SP, int NFINE>
 __global__ void __launch_bounds__(256) k_reflux_apply(GridConst G, Tables T, JobScalars J,
                                                      const int* __restrict__ tasks, int ntasks,
@@ -476,6 +476,10 @@ __global__ void __launch_bounds__(256) k_reflux_apply(GridConst G, Tables T, Job
   const long c = pidx(G, cc[0], cc[1], cc[2]);
   const double dt = J.dt_scale * J.dt[T.job[b]];
   void* o = block_ptr<SP>(out, b, G.pcells);
+  // (every load of a correction before its stores)
+  double u[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) u[q] = SP::ld(o, q, c, G.pcells);
   for (int a = d; a < ND; ++a) {
     const int f = a == 0 ? faces[0] : (a == 1 ? faces[1] : faces[ND - 1]);
     if (f < 0) continue;
@@ -505,9 +509,12 @@ __global__ void __launch_bounds__(256) k_reflux_apply(GridConst G, Tables T, Job
         Ff = (v[0][q] + v[1][q]) * R(0.5);
       const double df = (double)Ff - (double)F[q];
       const double dl = f & 1 ? -df * idx : df * idx;
-      SP::st(o, q, c, G.pcells, SP::ld(o, q, c, G.pcells) + w * dt * dl);
+      u[q] = u[q] + w * dt * dl;
+      if (SP::kBytesPerCell == StoreMixed::kBytesPerCell && q != I_EN) u[q] = (double)(float)u[q];  // as stored
     }
   }
+#pragma unroll
+  for (int q = 0; q < NV; ++q) SP::st(o, q, c, G.pcells, u[q]);
 }
 
 // CFL rate of the cells a flux correction changed (the coarse cells next to

@@ -723,6 +723,19 @@ int rebuild(amrvac_ctx* c) {
     trefl.insert(trefl.end(), J.t.trefl.begin(), J.t.trefl.end());
     for (int q = 0; q < 4; ++q) geom[4 * j + q] = J.t.geom[q];
   }
+  // flux-correction faces grouped by direction: waves beside each other then
+  // read alike (k_reflux_apply)
+  {
+    std::vector<int> by_dir;
+    by_dir.reserve(trefl.size());
+    for (int d = 0; d < 3; ++d)
+      for (size_t k = 0; k < trefl.size(); k += 2)
+        if ((trefl[k + 1] >> 1) == d) {
+          by_dir.push_back(trefl[k]);
+          by_dir.push_back(trefl[k + 1]);
+        }
+    trefl.swap(by_dir);
+  }
   int rc;
   std::vector<UploadItem> items;
   if ((rc = stage_list(c, &c->d_order, &c->cap_order, order, items)) ||
