@@ -458,7 +458,7 @@ __device__ __forceinline__ void hlld_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
   const R sl = fmin(ul, ur) - cfm, sr = fmax(ul, ur) + cfm;
   const R dl = (sl - ul) * rl, dr = (sr - ur) * rr;
   const R idd = rcp3_(dr - dl);
-  const R sm = (dr * ur - dl * ul - ptr + ptl) * idd;
+  R sm = (dr * ur - dl * ul - ptr + ptl) * idd;
   const R pts = (dr * ptl - dl * ptr + dl * dr * (ur - ul)) * idd;
   // single-star density and tangential parts, both sides.  With n = rho
   // (S - u)^2 - B_n^2 the denominator of the jump conditions is n - rho
@@ -466,6 +466,18 @@ __device__ __forceinline__ void hlld_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
   // their quotient alike.
   R isb[2], iden[2], num[2], den[2];
   rcp_pair(sl - sm, sr - sm, isb[0], isb[1]);
+  // (with pressures that are not positive S_M may fall on S_L or S_R, whose
+  // infinity a shared reciprocal, FP64's, would pass to the other side)
+  if constexpr (sizeof(R) == sizeof(double)) {
+    const bool apart = sl < sm && sm < sr;
+    if (__any(!apart)) {
+      asm volatile("");  // keeps the branch wave-uniform
+      if (!apart) {
+        isb[0] = rcp3_(sl - sm);
+        isb[1] = rcp3_(sr - sm);
+      }
+    }
+  }
   num[0] = dl * (sl - ul) - bn2;
   num[1] = dr * (sr - ur) - bn2;
   den[0] = num[0] - dl * (sm - ul);
@@ -498,33 +510,51 @@ __device__ __forceinline__ void hlld_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
   const R isum = rcp3_(sql + sqr);
   const R sg = bn > R(0) ? R(1) : (bn < R(0) ? R(-1) : R(0));
   const R sgq = sql * sqr * sg;
-  const R vss1 = (sql * v10 + sqr * v11 + (b11 - b10) * sg) * isum;
-  const R vss2 = (sql * v20 + sqr * v21 + (b21 - b20) * sg) * isum;
-  const R bss1 = (sql * b11 + sqr * b10 + sgq * (v11 - v10)) * isum;
-  const R bss2 = (sql * b21 + sqr * b20 + sgq * (v21 - v20)) * isum;
+  R vss1 = (sql * v10 + sqr * v11 + (b11 - b10) * sg) * isum;
+  R vss2 = (sql * v20 + sqr * v21 + (b21 - b20) * sg) * isum;
+  R bss1 = (sql * b11 + sqr * b10 + sgq * (v11 - v10)) * isum;
+  R bss2 = (sql * b21 + sqr * b20 + sgq * (v21 - v20)) * isum;
   // the side a of the contact the interface lies on, and its states
   const bool right = sr < R(0) || (!(sl > R(0)) && sm < R(0));
   const R rho = right ? rr : rl, u = right ? ur : ul, pt = right ? ptr : ptl, p = right ? wr[4] : wl[4];
   const R u1 = right ? wr[1 + T1] : wl[1 + T1], u2 = right ? wr[1 + T2] : wl[1 + T2];
   const R c1 = right ? wr[I_BX + T1] : wl[I_BX + T1], c2 = right ? wr[I_BX + T2] : wl[I_BX + T2];
   const R S = right ? sr : sl, sa = S - u;
-  const R rsa = right ? rs1 : rs0, isba = right ? isb[1] : isb[0];
-  const R vs1a = right ? v11 : v10, vs2a = right ? v21 : v20;
-  const R bs1a = right ? b11 : b10, bs2a = right ? b21 : b20;
+  const R isba = right ? isb[1] : isb[0];
+  R rsa = right ? rs1 : rs0;
+  R vs1a = right ? v11 : v10, vs2a = right ? v21 : v20;
+  R bs1a = right ? b11 : b10, bs2a = right ? b21 : b20;
   const R b2 = bn2 + (c1 * c1 + c2 * c2);
   const R v2 = u * u + u1 * u1 + u2 * u2;
   const R e = p * inv_gm1 + R(0.5) * rho * v2 + R(0.5) * b2;
   const R vb = u * bn + u1 * c1 + u2 * c2;
   const R vbs = sm * bn + vs1a * bs1a + vs2a * bs2a;
-  const R es = (sa * e - pt * u + pts * sm + bn * (vb - vbs)) * isba;
+  R es = (sa * e - pt * u + pts * sm + bn * (vb - vbs)) * isba;
   const R vbss = sm * bn + vss1 * bss1 + vss2 * bss2;
   const R sqa = right ? sqr : -sql;  // with the sign of the side
-  const R des = sqa * (vbs - vbss) * sg;  // e** - e*
+  R des = sqa * (vbs - vbss) * sg;  // e** - e*
   const R sas = sm + fabs(bn) * (right ? isqr : -isql);  // S*_a
   const bool super = sl > R(0) || sr < R(0);                        // every wave moves one way: F = F_a
   const bool inner = !super && (right ? sas : -sas) > R(0);          // between the Alfven wave and the contact
   // F = F_a + S (U* - U_a) + S* (U** - U*): the terms of waves that do not
-  // reach the interface drop by their factor
+  // reach the interface drop by their factor, once their states are finite.
+  // They are not where the fast speed is lost in rounding beside u (S = u on
+  // both sides leaves S_M undefined) or a pressure is not positive; es + des
+  // shows it, since every quotient above enters it.
+  const bool finite = isfinite(es + des);
+  if (__any(!finite)) {
+    asm volatile("");  // keeps the branch wave-uniform
+    if (!finite) {
+      if (super) {
+        rsa = rho, sm = u, es = e;
+        vs1a = u1, vs2a = u2, bs1a = c1, bs2a = c2;
+      }
+      if (!inner) {
+        vss1 = vs1a, vss2 = vs2a, bss1 = bs1a, bss2 = bs2a;
+        des = R(0);
+      }
+    }
+  }
   const R s1 = super ? R(0) : S, s2 = inner ? sas : R(0);
   const R ru = rho * u, m1 = rho * u1, m2 = rho * u2;
   F[I_RHO] = ru + s1 * (rsa - rho);
@@ -573,11 +603,11 @@ __device__ __forceinline__ void hllc_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
                      rr * wr[1 + T1] * ur - wr[I_BX + T1] * bn);
   const R m2h = havg(rl * wl[1 + T2], rr * wr[1 + T2], rl * wl[1 + T2] * ul - wl[I_BX + T2] * bn,
                      rr * wr[1 + T2] * ur - wr[I_BX + T2] * bn);
-  const R b1h = havg(wl[I_BX + T1], wr[I_BX + T1], ul * wl[I_BX + T1] - bn * wl[1 + T1],
+  R b1h = havg(wl[I_BX + T1], wr[I_BX + T1], ul * wl[I_BX + T1] - bn * wl[1 + T1],
                      ur * wr[I_BX + T1] - bn * wr[1 + T1]);
-  const R b2h = havg(wl[I_BX + T2], wr[I_BX + T2], ul * wl[I_BX + T2] - bn * wl[1 + T2],
+  R b2h = havg(wl[I_BX + T2], wr[I_BX + T2], ul * wl[I_BX + T2] - bn * wl[1 + T2],
                      ur * wr[I_BX + T2] - bn * wr[1 + T2]);
-  const R sm = (dr * ur - dl * ul + ptl - ptr) * idd;
+  R sm = (dr * ur - dl * ul + ptl - ptr) * idd;
   const R pts = dl * (sm - ul) + ptl;
   // the side of the contact the interface lies on
   const bool super = sl >= R(0) || sr <= R(0);
@@ -595,10 +625,19 @@ __device__ __forceinline__ void hllc_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
   const R e = p * inv_gm1 + R(0.5) * rho * v2 + R(0.5) * b2;
   const R vb = u * bn + u1 * c1 + u2 * c2;
   const R m1 = rho * u1, m2 = rho * u2, ru = rho * u;
-  const R rs = rho * sa * isb;
-  const R ms1 = (m1 * sa + bn * (c1 - b1h)) * isb;
-  const R ms2 = (m2 * sa + bn * (c2 - b2h)) * isb;
-  const R es = (e * sa - pt * u + pts * sm + bn * (vb - vbs)) * isb;
+  R rs = rho * sa * isb;
+  R ms1 = (m1 * sa + bn * (c1 - b1h)) * isb;
+  R ms2 = (m2 * sa + bn * (c2 - b2h)) * isb;
+  R es = (e * sa - pt * u + pts * sm + bn * (vb - vbs)) * isb;
+  // (a factor of zero drops only finite star states: see HLLD)
+  const bool finite = isfinite(es);
+  if (__any(!finite)) {
+    asm volatile("");  // keeps the branch wave-uniform
+    if (!finite && super) {
+      rs = rho, sm = u, es = e;
+      ms1 = m1, ms2 = m2, b1h = c1, b2h = c2;
+    }
+  }
   const R s1 = super ? R(0) : S;  // F = F_a + S (U* - U_a), F_a when every wave moves one way
   F[I_RHO] = ru + s1 * (rs - rho);
   F[1 + D] = ru * u + pt - bn2 + s1 * (rs * sm - ru);
