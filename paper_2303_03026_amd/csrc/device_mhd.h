@@ -349,18 +349,22 @@ struct Transverse {
 // Fast speeds along the normal on both sides of a face with the common
 // normal field (bn2 = B_n^2, t2 = |B_t|^2): c_f^2 = (S + sqrt(S^2 - 4 gamma p
 // B_n^2)) / (2 rho), S = gamma p + B^2, with the radicand written as the sum
-// of squares (gamma p - B^2)^2 + 4 gamma p B_t^2, which does not cancel; the
-// two 1/rho come from one reciprocal.
+// of squares (gamma p - B^2)^2 + 4 gamma p B_t^2, which does not cancel.
+// FP64: the two 1/rho come from one reciprocal.  FP32 divides by rho first:
+// the square of a pressure leaves its range from 1e19 up and from 1e-19 down,
+// whatever the speeds are.
 template <class R>
 __device__ __forceinline__ void cfast_faces(R rl, R rr, R pl, R pr, R t2l, R t2r, R bn2, R gamma, R& cl, R& cr) {
   R il, ir;
   rcp_pair(rl, rr, il, ir);
-  const R gl = gamma * pl, gr = gamma * pr;
-  const R b2l = bn2 + t2l, b2r = bn2 + t2r;
+  constexpr bool kScale = sizeof(R) < sizeof(double);
+  const R gl = kScale ? gamma * pl * il : gamma * pl, gr = kScale ? gamma * pr * ir : gamma * pr;
+  const R tl = kScale ? t2l * il : t2l, tr = kScale ? t2r * ir : t2r;
+  const R b2l = (kScale ? bn2 * il : bn2) + tl, b2r = (kScale ? bn2 * ir : bn2) + tr;
   const R ml = gl - b2l, mr = gr - b2r;
-  const R dl = ml * ml + (R(4) * gl) * t2l, dr = mr * mr + (R(4) * gr) * t2r;
-  cl = sqrt_pos(((gl + b2l) + sqrt_pos(dl)) * (R(0.5) * il));
-  cr = sqrt_pos(((gr + b2r) + sqrt_pos(dr)) * (R(0.5) * ir));
+  const R dl = ml * ml + (R(4) * gl) * tl, dr = mr * mr + (R(4) * gr) * tr;
+  cl = sqrt_pos(((gl + b2l) + sqrt_pos(dl)) * (kScale ? R(0.5) : R(0.5) * il));
+  cr = sqrt_pos(((gr + b2r) + sqrt_pos(dr)) * (kScale ? R(0.5) : R(0.5) * ir));
 }
 
 // Interface flux along D from reconstructed left/right primitive states:
