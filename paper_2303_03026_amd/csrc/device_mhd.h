@@ -523,16 +523,19 @@ __device__ __forceinline__ void hlld_glm_flux(R wl[NV], R wr[NV], R ch, R half_i
   f1[1] = bn * (sm - ur) * iden[1];
   f2[0] = num[0] * iden[0];
   f2[1] = num[1] * iden[1];
-  // the degenerate case is rare: its selects run only in waves that have it
+  // the degenerate case is rare: only waves that have it enter the branch, and
+  // only its lanes change (a face evaluated in two waves gives the same bits)
   const bool deg0 = !(fabs(den[0]) > R(1e-12) * (dl * (sl - ul))), deg1 = !(fabs(den[1]) > R(1e-12) * (dr * (sr - ur)));
   if (__any(deg0 || deg1)) {
     asm volatile("");  // keeps the branch wave-uniform
-    iden[0] = rcp3_(den[0]);
-    iden[1] = rcp3_(den[1]);
-    f1[0] = deg0 ? R(0) : bn * (sm - ul) * iden[0];
-    f1[1] = deg1 ? R(0) : bn * (sm - ur) * iden[1];
-    f2[0] = deg0 ? R(1) : num[0] * iden[0];
-    f2[1] = deg1 ? R(1) : num[1] * iden[1];
+    if (deg0 || deg1) {
+      iden[0] = rcp3_(den[0]);
+      iden[1] = rcp3_(den[1]);
+      f1[0] = deg0 ? R(0) : bn * (sm - ul) * iden[0];
+      f1[1] = deg1 ? R(0) : bn * (sm - ur) * iden[1];
+      f2[0] = deg0 ? R(1) : num[0] * iden[0];
+      f2[1] = deg1 ? R(1) : num[1] * iden[1];
+    }
   }
   const R v10 = wl[1 + T1] - f1[0] * wl[I_BX + T1], v11 = wr[1 + T1] - f1[1] * wr[I_BX + T1];
   const R v20 = wl[1 + T2] - f1[0] * wl[I_BX + T2], v21 = wr[1 + T2] - f1[1] * wr[I_BX + T2];
