@@ -75,11 +75,13 @@ __device__ __forceinline__ long cell5(const GridConst& G, int x, int y, int z = 
 // maximum (C.rate_bits, C.nan), leaving out the cells next to faces towards
 // finer leaves when C.skip_fine (the flux correction changes them later).
 // Workgroups per CU (waves per SIMD): three in FP64 (at most 168 VGPRs; the
-// instances take 133 to 168), four in FP32-mixed (128).
-template <class SP>
-constexpr int kWavesPerEU5 = SP::kBytesPerCell == 72 ? 3 : 4;
+// instances take 133 to 168), four in FP32-mixed (128), but three with the
+// two-ghost-layer limiters: bound to 128, HLLD's instance of theirs (104) was
+// scheduled so that a 96^3 step took 0.84 ms, against 0.69.
+template <class SP, int LIM>
+constexpr int kWavesPerEU5 = SP::kBytesPerCell == 72 || LIM < 0 ? 3 : 4;
 template <int NDIM, class SP, bool W1, bool CFL, int LIM, int FLX>
-__global__ void __launch_bounds__(256, kWavesPerEU5<SP>) k_stage_fused5(GridConst G, Tables T, JobScalars J, const void* __restrict__ in,
+__global__ void __launch_bounds__(256, (kWavesPerEU5<SP, LIM>)) k_stage_fused5(GridConst G, Tables T, JobScalars J, const void* __restrict__ in,
                                                          const void* base, void* out, double wgt, PhysConst P,
                                                          DevStatus* st, double* __restrict__ part,
                                                          typename SP::R* __restrict__ freg, JobCfl C) {
