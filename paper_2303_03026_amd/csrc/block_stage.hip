@@ -213,8 +213,6 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
     }
     halo(k0, tc);
   }
-  // plane k+2 is loaded a plane's faces ahead where the registers allow it
-  constexpr bool kPrefetch = NDIM == 3 && LIM == LIM_VANLEER && FLX == FLUX_HLL;
   const int tcol = tc;
   for (int k = k0; k < k1; ++k) {
     // the column again, for this plane's addresses (see the fused stage)
@@ -222,8 +220,6 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
     if (NDIM == 3) asm volatile("" : "+v"(tc));
     const int i = tc % nx, j = tc / nx;
     const int kofs = NDIM == 3 ? k * nx : 0;
-    double uc[NV];
-    if (kPrefetch && live) load_z(i, j, k + 2, uc);
     lds_barrier();  // the plane is complete
     if (live) {
       for (int l = tc; l < 2 * nx; l += S.cols) {  // far faces: x lines, then y lines
@@ -256,10 +252,12 @@ __global__ void __launch_bounds__(256, 2) k_stage_block(GridConst G, Tables T, J
       const int c = cell(i, j, k);
       double fz[NV];
       if (NDIM == 3) {
-        double wa[NV], wc[NV], wl[NV], wr[NV];
+        // (plane k+2 loaded here, not a plane's faces ahead: no registers are
+        // left for it, and the spills took 512 blocks of 8^3 108 against 101 us)
+        double uc[NV], wa[NV], wc[NV], wl[NV], wr[NV];
 #pragma unroll
         for (int q = 0; q < NV; ++q) wa[q] = Wp[at(i, j) + q];
-        if (!kPrefetch) load_z(i, j, k + 2, uc);
+        load_z(i, j, k + 2, uc);
         convert(uc, wc, owns(k + 2));
         for_increments<LIM, double>([&](int q, double& m, double& w, double& p) { m = wa[q]; w = wb[q]; p = wc[q]; },
                                     [&](int q, double w, double r, double l) {
