@@ -131,7 +131,9 @@ int amrvac_slot_bytes(const amrvac_grid_desc* g, int nblocks, size_t* bytes);
  * of amrvac_slot_bytes each (nslots >= 3 for SSPRK(3,3) stepping); stream is
  * a hipStream_t (NULL = the null stream).  The library builds its neighbour
  * and ghost task tables on the host, uploads them and allocates its own
- * scratch (primitive and face-flux buffers, reduction scalars). */
+ * scratch (reduction scalars here; flux registers, or the primitives and face
+ * fluxes of the per-kernel path's five-cell reconstructions, on the first
+ * stage that needs them). */
 int amrvac_init_blocks(amrvac_ctx** out, const amrvac_grid_desc* g, int nblocks,
                        const int* level, const int* ijk, void* const* slots, int nslots,
                        void* stream);
@@ -195,16 +197,18 @@ int amrvac_stage_cfl(amrvac_ctx* c, int in_slot, int base_slot, int out_slot, do
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * amrvac_stage on the per-kernel (plain) FP64 path, with the same arguments,
- * checks and result bit for bit, whose primitive and face-flux scratch is a
+ * checks and result bit for bit, whose scratch (primitives and face fluxes
+ * with the five-cell reconstructions, flux registers with the others) is a
  * static device array of AMRVAC_NOALLOC_SCRATCH_BYTES held by each GPU from
  * the library's load until the process ends, instead of library allocations.
  * It calls no allocating routine.  It runs the per-kernel kernels whatever
  * path the context is set to; FP64 single-job contexts only (else
- * AMRVAC_E_ARG, batch contexts AMRVAC_E_STATE).  A grid whose scratch
- * (blocks x 9 x 8 B x (padded cells + ndim x faces per block), each part
- * rounded up to 256 B) exceeds the array is rejected with AMRVAC_E_ARG and
- * a message giving both sizes: 3D blocks of 16^3 need 1.52 MB each (up to
- * 44 blocks), 2D blocks of 16^2 68 KB (up to 987).  Every call on a GPU
+ * AMRVAC_E_ARG, batch contexts AMRVAC_E_STATE).  A grid whose primitives and
+ * face fluxes (blocks x 9 x 8 B x (padded cells + ndim x faces per block),
+ * each part rounded up to 256 B) exceed the array is rejected with
+ * AMRVAC_E_ARG and a message giving both sizes, whatever the reconstruction
+ * (the others need less, but the limit is one): 3D blocks of 16^3 count 1.52
+ * MB each (up to 44 blocks), 2D blocks of 16^2 68 KB (up to 987).  Every call on a GPU
  * shares that GPU's array: calls that overlap in time on one GPU (other
  * streams, other contexts, other threads) race and must be ordered by the
  * caller.  No part of the array needs to start cleared. */
@@ -292,11 +296,13 @@ int amrvac_regrid(amrvac_ctx* c, int slot, int nb, const int* level, const int* 
  * AMRVAC_E_ARG for bad arguments, AMRVAC_E_STATE on batch contexts. */
 int amrvac_lohner(amrvac_ctx* c, int slot, const double* weights, double wavefilter, double* indicator_dev);
 
-/* Select the stage implementation: AMRVAC_PATH_PLAIN (separate primitive,
- * per-direction flux, reflux and update kernels; FP64 only, the default for
- * FP64 contexts) or AMRVAC_PATH_FUSED (one kernel per stage plus, on AMR
- * grids, a coarse/fine flux correction; needs block_nx = 16; the only path
- * of FP32-mixed contexts).
+/* Select the stage implementation: AMRVAC_PATH_PLAIN (any block size; one
+ * kernel per stage and block with the two-ghost-layer limiters, separate
+ * primitive, per-direction flux, reflux and update kernels with the five-cell
+ * reconstructions; FP64 only, the default for FP64 contexts) or
+ * AMRVAC_PATH_FUSED (one kernel per stage plus, on AMR grids, a coarse/fine
+ * flux correction; needs block_nx = 16; the only path of FP32-mixed
+ * contexts).
  * AMRVAC_E_ARG if the context cannot run it. */
 int amrvac_set_path(amrvac_ctx* c, int path);
 
@@ -305,9 +311,9 @@ int amrvac_set_path(amrvac_ctx* c, int path);
  *   zseg:   workgroups per 3D block, each marching 16/zseg of its z planes
  *           (1, 2 or 4; 1 in 2D).  More, shorter workgroups fill the GPU on
  *           small grids at the cost of re-reading 4 planes per segment.
- *   rotate: 1 rotates the per-plane extra work (halo cells, halo slopes and
- *           the 17th face of each line) over the four waves of a workgroup,
- *           0 leaves it to the first waves.
+ *   rotate: 1 rotates the per-plane extra work (halo cells and the 17th face
+ *           of each line) over the four waves of a workgroup, 0 leaves the
+ *           halo cells to the first two waves and the 17th faces to the third.
  *   xcd:    1 gives each of the 8 XCDs a contiguous run of the Morton-ordered
  *           block list (neighbours share an L2), 0 deals workgroups out in
  *           list order.

@@ -6,13 +6,19 @@
 // It replaces launches that passed primitives and face fluxes through memory
 // (a padded state written and read once per direction, three face arrays
 // written and read: about 15 times the state, where this reads it once, with
-// its neighbours' rims, and writes it once).  Van Leer + HLL, one SSPRK(2,2)
-// step with CFL and ghost fill, before -> now: 512 blocks of 8^3 713 -> 187 us
-// (311 while the ghost cells of same-level faces were still filled), of 16^3
-// 4959 -> 1199 us; 1024 2D blocks of 8^2 (cada3 + HLLC) 73 -> 37 us per step;
-// 2309 blocks of 8^3 on three levels 2033 -> 582 us.  Bound by issue: three
-// faces per cell at two waves per SIMD (the 3D instances use all 256
-// registers), with the halo cells and far faces of short lines on top.
+// its neighbours' rims, and writes it once).  Van Leer + HLL, a captured
+// SSPRK(2,2) step, before -> now: 512 blocks of 8^3 255 -> 101 us, of 16^3
+// 1648 -> 427 us, 8 blocks of 16^3 103 -> 52; 1024 2D blocks of 8^2 (cada3 +
+// HLLC) 98 -> 47 us; an SSPRK(3,3) step of 2309 blocks of 8^3 on three levels
+// 2030 -> 560 us.
+//
+// What bounds it, by counters: memory traffic.  256^3 in blocks of 16^3 moves
+// 7.1 (w = 1) and 8.8 GB (w < 1) a launch at 4.9 and 5.3 TB/s, where a device
+// copy reaches 4.7, with 1478 and 1489 VALU instructions a cell, 37 to 43% of
+// the issue peak; 2309 blocks of 8^3 move 0.9 GB at 4.9 TB/s, with 1900 VALU
+// instructions a cell (halo cells and far faces of short lines), 31% of the
+// peak, in 2309 waves on the 2048 places of two waves per SIMD (the 3D
+// instances take 249 to 256 registers).
 //
 // Thread t of a workgroup owns the column (i, j) = (t % nx, t / nx) and
 // marches through its planes; the z stencil is a register queue (as in the

@@ -740,7 +740,8 @@ __device__ __forceinline__ void weno5_sides(double vm2, double vm1, double v0, d
   // the three reciprocals of the weights come from one reciprocal of their
   // product (the refined hardware reciprocal is the costly operation here);
   // the factors are at least 4e-40 (1.6e-11 for 'weno5'), so the product does
-  // not underflow, and it overflows only for cell values beyond about 1e50
+  // not underflow.  It is of the sixth power of the differences (the twelfth
+  // for 'weno5') and overflows for values beyond about 1e50 (1e25).
   auto rcp_three = [](double x0, double x1, double x2, double& r0, double& r1, double& r2) {
     const double x02 = x0 * x2;
     const double r = rcp3_(x02 * x1);

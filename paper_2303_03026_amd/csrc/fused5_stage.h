@@ -68,9 +68,9 @@ __device__ __forceinline__ long cell5(const GridConst& G, int x, int y, int z = 
 // in these flux registers ([block][face][var][face cell], face cell t1 + 16
 // t2 with t1 along the face's first transverse axis: y for x faces, x
 // otherwise) for the correction pass.  One instance serves both cases: a
-// separate instance without the register stores was measured slower (its
-// register allocation spills 448 against 176 B per lane in 3D FP64, and a
-// c1 step with 'wenozp5' + HLLC took 19.3 against 16.5 ms).
+// separate one without the register stores spills 7 to 69 registers in FP64,
+// where this one spills none (HLLD: 3 to 9), and a 256^3 step with 'wenozp5'
+// takes 10.5 against 10.2 ms (HLLC) and 13.7 against 10.7 (HLLD).
 // CFL: also fold the CFL rate of every output cell into the job's running
 // maximum (C.rate_bits, C.nan), leaving out the cells next to faces towards
 // finer leaves when C.skip_fine (the flux correction changes them later).

@@ -29,11 +29,13 @@
 // from that neighbour's interior; only faces towards finer or coarser
 // leaves and physical boundaries need filled ghost cells.
 //
-// What bounds it (256^3, FP64, one launch): its loads and stores alone take
-// 0.97 ms (w = 1) and 1.23 ms (w < 1), its arithmetic alone 0.90 and 1.02 ms,
-// the launch 1.11 to 1.24 ms.  With both slopes of every face formed by the
-// face's own lane (and the 17th faces by two waves, each from scratch) it
-// was 1.55 and 1.76 ms: 1934 VALU instructions per cell, now 1204.
+// What bounds it (256^3, FP64, one launch): memory traffic.  Its loads and
+// stores alone took 0.97 ms (w = 1) and 1.23 ms (w < 1), measured with the
+// arithmetic left out; the launch takes 1.20 and 1.27 to 1.42 ms, with 1294 and
+// 1320 VALU instructions a cell, which the issue peak would take 0.55 and 0.56
+// ms for.  With both slopes of every face formed by the face's own lane (and
+// the 17th faces by two waves, each from scratch) it was 1.55 and 1.76 ms at
+// 1934 instructions.
 #pragma once
 #include <type_traits>
 
@@ -119,7 +121,7 @@ struct FaceConst {
 };
 
 // Waves per SIMD the stage is built for: FP64 3D holds the z queue beside a
-// face evaluation (two waves, 230-256 VGPRs); in 2D there is no z queue and
+// face evaluation (two waves, 220-256 VGPRs); in 2D there is no z queue and
 // three waves fit in FP64 (the LDS of a fourth would not) and five in mixed.
 template <class SP>
 constexpr int kWavesPerEU2D = SP::kBytesPerCell == 72 ? 3 : 5;

@@ -106,8 +106,8 @@ hipError_t launch_update(hipStream_t s, const GridConst& G, const Tables& T, con
 // Launch shape of the fused stage (results do not depend on it):
 //   zseg: workgroups per block, each marching BN / zseg z planes (1, 2, 4;
 //         3D only)
-//   rot:  rotate the per-plane extra work (halo cells, halo slopes, 17th
-//         faces) over the four waves of a workgroup
+//   rot:  rotate the per-plane extra work (halo cells, 17th faces) over the
+//         four waves of a workgroup
 //   xcd:  give each XCD a contiguous run of the block list
 struct FusedTune {
   int zseg;
